@@ -1,27 +1,36 @@
-// Grouped expert GEMMs for large token counts (prefill): the SwiGLU FFN of Eq. 6
-// over every HIT expert's bucket and over all tokens for the shared block
-// (Sec. 2.1, 4.2), as dense MFMA contractions.  bf16 operands, fp32 accumulation.
+// Grouped expert GEMMs for many tokens (prefill and large decode batches), bf16 activations:
+// the SwiGLU FFN of Eq. 6 over every HIT expert's bucket and over all tokens for the shared
+// block (Sec. 2.1, 4.2), and the LoRE correction of Eq. 9 over every LORE bucket.
 //
 //   up   : H[pos][f] = silu(sum_k W1[f][k] x[k]) * (sum_k W3[f][k] x[k])   (bf16 out)
+//          U[pos][q] = sum_k A[q][k] x[k]                                  (fp32 out)
 //   down : Y[pos][j] = sum_k W2[j][k] H[pos][k]                            (fp32 out)
+//          D[pos][j] = sum_q B[j][q] U[pos][q]     (fp32 MFMA: U is not rounded; fp32 out)
 //
-// Block tile: 256 weight rows x 256 tokens, 64 k per stage, 8 waves of 128 weight rows x
-// 64 tokens (LDS traffic is 43 flop per byte read).  For `up` the 256 weight rows are 128
-// W1 rows and the same 128 W3 rows, so each wave holds the gate and up sums of its 64
-// features and applies SwiGLU in registers.  The weight tile is the MFMA A operand and
-// the token tile the B operand (v_mfma_f32_16x16x32_bf16): a lane ends with 4 consecutive
-// features of one token, stored with one 8- (bf16) or 16-byte (fp32) write.  A wave's
-// token sub-tiles are interleaved with the other waves' (rows 64 t + 16 wt), so the ragged
-// last tile of an expert spreads over the SIMDs and sub-tiles without a live token issue
-// no MFMA.
-// Both tiles are staged through LDS (two stages, 128 KiB: one block per CU) in
+// A block computes a tile of BM weight rows x BT tokens over the whole contraction, 64 k per
+// stage (v_mfma_f32_16x16x32_bf16, weights as the A operand, tokens as B).  For `up` the rows
+// are BM / 2 W1 rows and the same W3 rows, so a wave holds the gate and up sums of its
+// features and applies SwiGLU in registers.  A wave's token sub-tiles are interleaved with the
+// other waves' (rows kTStride t + 16 wt), so the ragged last tile of an expert spreads over
+// the SIMDs; sub-tiles without a live token are not read and issue no MFMA, and their rows are
+// not fetched.
+//
+// Staging: buffer loads straight to LDS (no staging registers) into a ring of S stages of
 // 128-byte rows whose 16-byte chunks are XOR-swizzled by row (chunk c of row r at
-// c ^ ((r >> 1) & 7)), so fragment reads are free of bank conflicts.  The global loads of
-// the next stage go straight to LDS (global_load_lds_dwordx4, no staging registers), issued
-// before the MFMAs of the current one by waves 0-3 only.  Token rows of an expert are
-// gathered through perm once per tile.
-// Tiles: the shared block first, then the HIT experts in id order; inside a group
-// the token tiles of one weight tile are consecutive (the weight tile is then
+// c ^ ((r >> 1) & 7)): free of bank conflicts for the fragment reads and the DMA writes.  A
+// chunk past the end of a row, and a row past the end of a matrix or a bucket, reads zero (an
+// offset past the buffer), so no size has to be a multiple of the tile.
+// Pipeline: the fragments of a stage's two k-steps are read half a stage ahead of their MFMAs,
+// so a wave reads LDS while its MFMAs run; one barrier per stage, in the middle of the MFMAs,
+// frees the buffer just read for the stage S ahead.
+// What bounds it: with short buckets, the weight stream from HBM (bytes in flight: S - 1 stages
+// per block), with long ones the MFMAs (960 - 1020 TFLOP/s at Qwen2 sizes, T = 4096).  Against
+// one 256 x 256 two-stage shape for every T, with 32 or more tokens per pass of the streaming
+// tiles below T = 256 and separate LoRE launches (us per layer call, DeepSeek-V2-Lite sizes):
+// T = 64 204 -> 187, T = 192 259 -> 209, T = 300 311 -> 189, T = 1000 357 -> 263, T = 4096 of
+// Qwen2 3661 -> 3581; Qwen2 T = 96 882 -> 604, T = 300 1325 -> 884 (its shared block split).
+// Tiles: the shared block first, then the HIT experts in id order, then the LORE buckets;
+// inside a group the token tiles of one weight tile are consecutive (the weight tile is then
 // served from L2), and consecutive tiles are kept on one XCD.
 #include <hip/hip_runtime.h>
 
@@ -32,25 +41,40 @@
 namespace spice {
 namespace {
 
-constexpr int kWaveT = 64;                     // tokens per wave (a wave holds 128 features x kWaveT)
-constexpr int kThreads = 64 * 2 * (256 / kWaveT);  // 2 (features) x 256 / kWaveT (tokens) waves
-constexpr int kBM = 256;                       // weight rows per tile
-constexpr int kBT = 256;                       // tokens per tile
-constexpr int kBK = 64;                        // contraction per stage (32 or 64)
-constexpr int kWavesPerEU = kWaveT == 128 ? 1 : 2;  // waves per SIMD the register budget targets
-constexpr int kTS = kWaveT / 16;               // token sub-tiles per wave
-constexpr int kTStride = 16 * (kBT / kWaveT);  // tile rows between a wave's token sub-tiles
-constexpr int kXcdBlocks = 32;                 // blocks one XCD runs at a time (32 CUs, 1 block each)
-constexpr int kRowBytes = kBK * 2;             // bytes of a staged row
-constexpr int kCPR = kBK / 8;                  // 16-byte chunks per staged row
-constexpr int kWTile = kBM * kRowBytes;        // weight tile of one stage
-constexpr int kStageLds = (kBM + kBT) * kRowBytes;
-constexpr int kLoaders = kThreads / 2;         // waves 0-3 issue every global load, one per SIMD
-constexpr int kRowStep = kLoaders / kCPR;      // staging rows between a loader's chunks
-constexpr int kWChunks = kBM * kCPR / kLoaders;  // 16-byte weight chunks per loader per stage
-constexpr int kXChunks = kBT * kCPR / kLoaders;  // 16-byte token chunks per loader per stage
-constexpr int kUpFeat = kBM / 2;               // features of an up tile (W1 rows = W3 rows)
-static_assert(kBK == 32 || kBK == 64, "a stage is one or two MFMA k-steps");
+// Tile shapes: BM weight rows x BT tokens, a grid of WF x WT waves, S stages in LDS, W waves
+// per SIMD the register budget targets, L waves that issue the stages' loads.  Of the big tile's
+// eight waves four load, one per SIMD, so the others' MFMAs never wait behind the load queue
+// (Qwen2, T = 4096: 3764 -> 3633 us).  Measured beside them and slower over their ranges:
+// 128 x 128 (2 or 4 stages), 64 x 64, 128 x 32 and 256 x 64 tiles.
+template <int BM_, int BT_, int WF_, int WT_, int S_, int W_, int L_>
+struct Shape {
+    static constexpr int BM = BM_, BT = BT_, WF = WF_, WT = WT_, S = S_, W = W_;
+    static constexpr int kThreads = 64 * WF * WT;
+    static constexpr int kLoaders = 64 * L_;
+    static constexpr int RF = BM / WF / 16;      // 16-row sub-tiles per wave
+    static constexpr int RT = BT / WT / 16;      // 16-token sub-tiles per wave
+    static constexpr int kTStride = 16 * WT;     // tile rows between a wave's token sub-tiles
+    static constexpr int kUpFeat = BM / 2;       // features of an up tile (W1 rows = W3 rows)
+    static constexpr int kWTile = BM * 128;      // bytes of a stage's weight rows
+    static constexpr int kStage = (BM + BT) * 128;
+    static constexpr int kRowStep = kLoaders / 8;  // rows one load instruction of the loaders covers
+    static constexpr int kWLoads = BM / kRowStep, kXLoads = BT / kRowStep;
+    static constexpr int kXcdBlocks = 32 * std::max(1, 163840 / (S * kStage));  // resident blocks per XCD
+    static_assert(kRowStep % 16 == 0 && kUpFeat % kRowStep == 0, "staged rows keep their swizzle");
+    static_assert(BM % kRowStep == 0 && BT % kRowStep == 0, "whole load instructions");
+    static_assert((S - 2) * (kWLoads + kXLoads) < 64, "vmcnt holds the loads in flight");
+};
+using Big = Shape<256, 256, 2, 4, 2, 2, 4>;
+using Wide = Shape<256, 128, 4, 2, 3, 2, 8>;
+using Small = Shape<128, 64, 2, 2, 3, 2, 4>;
+static_assert(Big::BM == kGemmBigTile[0] && Big::BT == kGemmBigTile[1] && Wide::BM == kGemmWideTile[0] && Wide::BT == kGemmWideTile[1] && Small::BM == kGemmSmallTile[0] &&
+                  Small::BT == kGemmSmallTile[1],
+              "the shapes' tiles as the split rule knows them");
+
+constexpr int kBK = 64;                          // contraction per stage
+constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;    // an offset past every buffer
+constexpr long long kMaxBuffer = 0xFFFF0000ll;   // bytes a buffer may hold
+constexpr int kRawBufferWord3 = 0x00020000;      // gfx9 raw buffer: 32-bit data format
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -64,43 +88,88 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
 
 __device__ __forceinline__ float silu(float u) { return u / (1.0f + __expf(-u)); }
 
-// Logical tile of block b.  The hardware deals blocks to the 8 XCDs round robin
-// (block b to XCD b % 8).  Here every round of 8 x 32 blocks gives each XCD 32
-// consecutive logical tiles (neighbouring tiles share operands in that XCD's L2),
-// and the rounds alternate over all XCDs so that long tiles at the front of the
-// order spread over the whole chip.  A final partial round keeps block order; the
-// map is a bijection on [0, G).
-__device__ __forceinline__ int xcd_tile(int b, int G) {
-    constexpr int kRound = 8 * kXcdBlocks;
-    if (b >= (G / kRound) * kRound) return b;
+// Logical tile of block b.  The hardware deals blocks to the 8 XCDs round robin (block b to
+// XCD b % 8).  Here every round of 8 x per_xcd blocks gives each XCD per_xcd consecutive
+// logical tiles (neighbouring tiles share operands in that XCD's L2), and the rounds
+// alternate over all XCDs so that long tiles at the front of the order spread over the whole
+// chip.  A final partial round keeps block order; the map is a bijection on [0, G).
+__device__ __forceinline__ int xcd_tile(int b, int G, int per_xcd) {
+    const int round = 8 * per_xcd;
+    if (b >= (G / round) * round) return b;
     const int x = b & 7, slot = b >> 3;
-    return (slot / kXcdBlocks) * kRound + x * kXcdBlocks + slot % kXcdBlocks;
+    return (slot / per_xcd) * round + x * per_xcd + slot % per_xcd;
 }
 
+enum : int { kTileHit = 0, kTileShared = 1, kTileLore = 2 };
+
 struct TileJob {
-    const uint16_t* w;    // weight matrix of the group (rows of W13 or W2)
-    const uint16_t* act;  // activations: x (up) or H / Hs (down)
+    int kind;
+    const void* w;        // weight matrix of the group (W13, W2, A or B of one expert)
+    uint32_t w_bytes;     // its size
     int kdim;             // contraction length
-    int ld;               // row stride (elements) of the activations inside one stage
-    uint32_t kst;         // elements between consecutive stages of one activation row
-    int wrow0;            // first weight row of this tile (up: W1 row; W3 row = wrow0 + up_off)
-    int up_off;           // up: row distance from W1 to W3 inside w
-    int tok0, ntok;       // tile's first bucket position / token count of the group
-    int start;            // group's first bucket position (HIT) or 0 (shared)
-    bool gather;          // activation rows via perm (up of a HIT expert)
-    int feat0;            // first output feature of the tile
-    bool shared;
+    int nfeat;            // output features of the group
+    int up_off;           // up: rows from a tile row of the first half to its partner of the second
+    int row0;             // first weight row (= output feature) of the tile
+    int k0, k1;           // stages of the contraction this tile takes (all, but for a split shared block)
+    int part;             // which of the shared block's partial results it is
+    int tok0, ntok;       // tile's first token of the group / token count of the group
+    int start;            // group's first bucket position (0 for the shared block)
 };
 
-// Resolve logical tile L of a launch.  Returns false for tiles past the live work.
-template <bool kUp>
-__device__ bool resolve(const GemmArgs& a, int L, TileJob& j, int* s_scan) {
+// The bucket of class c holding tile L of nt tiles per token tile, found by a wave's scan of
+// the offsets; L is reduced by the class's tiles when it lies past them.
+__device__ bool scan_class(const GemmArgs& a, int c, int nt, int BT, int& L, int lane, int& e_, int& st_, int& n_,
+                           int& slot_) {
+    const int32_t* off = a.offsets + c * (a.N + 1);
+    for (int e0 = 0; e0 < a.N; e0 += 64) {
+        const int e = e0 + lane;
+        int st = 0, n = 0, slot = -1;
+        if (e < a.N) {
+            st = off[e];
+            n = off[e + 1] - st;
+            if (c == SPICE_CLASS_HIT) slot = a.resident_slot[e];
+        }
+        const int tiles = n > 0 ? ((n + BT - 1) / BT) * nt : 0;
+        int incl = tiles;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(incl, o);
+            if (lane >= o) incl += up;
+        }
+        const int excl = incl - tiles;
+        const unsigned long long bal = __ballot(tiles > 0 && L >= excl && L < incl);
+        if (bal) {
+            const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)bal) - 1);
+            e_ = e0 + src;
+            st_ = __builtin_amdgcn_readlane(st, src);
+            n_ = __builtin_amdgcn_readlane(n, src);
+            slot_ = __builtin_amdgcn_readlane(slot, src);
+            L -= __builtin_amdgcn_readlane(excl, src);
+            return true;
+        }
+        L -= __builtin_amdgcn_readlane(incl, 63);
+    }
+    return false;
+}
+
+// Resolve logical tile L of a launch; every wave does it for itself (uniform values).
+// Returns false for tiles past the live work.
+template <bool kUp, class C>
+__device__ bool resolve(const GemmArgs& a, int L, TileJob& j) {
     const int lane = threadIdx.x & 63;
-    const int nt_sh = kUp ? a.Is / kUpFeat : a.d / kBM;  // weight tiles of the shared block
-    const int nt_e = kUp ? a.I / kUpFeat : a.d / kBM;    // weight tiles of a routed expert
-    const int mt_sh = (a.T + kBT - 1) / kBT;
-    const int tiles_sh = a.Is > 0 ? nt_sh * mt_sh : 0;
+    constexpr int feat = kUp ? C::kUpFeat : C::BM;
+    const int d = a.d, I = a.I, Is = a.Is;
+    const int nt_sh = ((kUp ? Is : d) + feat - 1) / feat;  // weight tiles of the shared block
+    const int nt_e = ((kUp ? I : d) + feat - 1) / feat;    // of a routed expert
+    const int nt_l = ((kUp ? a.r : d) + C::BM - 1) / C::BM;  // of a LORE expert
+    const int mt_sh = (a.T + C::BT - 1) / C::BT;
+    const int parts = kUp ? 1 : a.parts, per_part = nt_sh * mt_sh;
+    const int tiles_sh = Is > 0 ? per_part * parts : 0;
+    j.k0 = 0;
+    j.part = 0;
     if (L < tiles_sh) {
+        j.part = L / per_part;
+        L -= j.part * per_part;
         // groups of sn weight tiles x sm token tiles (about one XCD's worth of blocks)
         // run together and share their operand tiles in that XCD's L2
         const int sn = kUp ? a.super_up[0] : a.super_dn[0], sm = kUp ? a.super_up[1] : a.super_dn[1];
@@ -108,288 +177,415 @@ __device__ bool resolve(const GemmArgs& a, int L, TileJob& j, int* s_scan) {
         const int mg = mt_sh / sm;
         const int n = (g / mg) * sn + in / sm;
         const int m = (g % mg) * sm + in % sm;
+        j.kind = kTileShared;
         j.w = kUp ? a.w13s : a.w2s;
-        j.act = kUp ? a.x : a.hs;
-        j.kdim = kUp ? a.d : a.Is;
-        j.ld = kUp ? a.d : kBK;
-        j.kst = kUp ? kBK : (uint32_t)a.T * kBK;
-        j.wrow0 = kUp ? n * kUpFeat : n * kBM;
-        j.up_off = a.Is;
-        j.tok0 = m * kBT;
+        j.w_bytes = (uint32_t)(kUp ? 2 : 1) * (uint32_t)Is * (uint32_t)d * 2u;
+        j.kdim = kUp ? d : Is;
+        const int nk = (j.kdim + kBK - 1) / kBK;
+        j.k0 = j.part * nk / parts;
+        j.k1 = (j.part + 1) * nk / parts;
+        j.nfeat = kUp ? Is : d;
+        j.up_off = Is;
+        j.row0 = n * feat;
+        j.tok0 = m * C::BT;
         j.ntok = a.T;
         j.start = 0;
-        j.gather = false;
-        j.feat0 = j.wrow0;
-        j.shared = true;
         return true;
     }
     L -= tiles_sh;
-    // HIT experts: tiles_e = ceil(n_e / kBT) * nt_e, in expert id order (one wave scans)
-    if (threadIdx.x < 64) {
-        int base = 0, found = -1;
-        for (int e0 = 0; e0 < a.N && found < 0; e0 += 64) {
-            const int e = e0 + lane;
-            int st = 0, n = 0;
-            if (e < a.N) {
-                st = a.offsets[e];
-                n = a.offsets[e + 1] - st;
-            }
-            const int tiles = n > 0 ? ((n + kBT - 1) / kBT) * nt_e : 0;
-            int incl = tiles;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(incl, o);
-                if (lane >= o) incl += up;
-            }
-            const int excl = base + incl - tiles;
-            const bool mine = tiles > 0 && L >= excl && L < excl + tiles;
-            const unsigned long long bal = __ballot(mine);
-            if (bal) {
-                const int src = __ffsll((long long)bal) - 1;
-                if (lane == src) {
-                    s_scan[0] = e;
-                    s_scan[1] = st;
-                    s_scan[2] = n;
-                    s_scan[3] = L - excl;
-                }
-                found = 1;
-            }
-            base += __shfl(incl, 63);
-        }
-        if (lane == 0 && found < 0) s_scan[0] = -1;
+    int e = 0, st = 0, n = 0, slot = -1;
+    int kind = kTileHit, nt = nt_e;
+    bool found = a.do_hit && scan_class(a, SPICE_CLASS_HIT, nt_e, C::BT, L, lane, e, st, n, slot);
+    if (!found) {
+        kind = kTileLore;
+        nt = nt_l;
+        found = a.r > 0 && scan_class(a, SPICE_CLASS_LORE, nt_l, C::BT, L, lane, e, st, n, slot);
     }
-    __syncthreads();
-    const int e = s_scan[0];
-    if (e < 0) return false;
-    const int st = s_scan[1], n = s_scan[2], t = s_scan[3];
+    if (!found) return false;
     if (st < 0 || n <= 0 || st + n > a.T * a.K) {
         if (threadIdx.x == 0) atomicOr(&a.ctrl[kWordFlags], (uint32_t)SPICE_FLAG_BAD_INDEX);
         return false;
     }
-    const int slot = a.resident_slot[e];
-    if (slot < 0 || slot >= a.C) {
-        if (threadIdx.x == 0) atomicOr(&a.ctrl[kWordFlags], (uint32_t)SPICE_FLAG_BAD_SLOT);
-        return false;
-    }
-    const int mt = (n + kBT - 1) / kBT;
-    const int nn = t / mt, m = t - nn * mt;
-    if (kUp) {
-        j.w = a.w13_pool + (size_t)slot * 2 * a.I * a.d;
-        j.act = a.x;
-        j.kdim = a.d;
-        j.ld = a.d;
-        j.kst = kBK;
-        j.wrow0 = nn * kUpFeat;
-        j.up_off = a.I;
-    } else {
-        j.w = a.w2_pool + (size_t)slot * a.d * a.I;
-        j.act = a.h;
-        j.kdim = a.I;
-        j.ld = kBK;
-        j.kst = (uint32_t)a.T * a.K * kBK;
-        j.wrow0 = nn * kBM;
-        j.up_off = 0;
-    }
-    j.tok0 = m * kBT;
+    const int mt = (n + C::BT - 1) / C::BT;
+    const int nn = L / mt, m = L - nn * mt;
+    j.kind = kind;
+    j.tok0 = m * C::BT;
     j.ntok = n;
     j.start = st;
-    j.gather = kUp;
-    j.feat0 = j.wrow0;
-    j.shared = false;
+    if (kind == kTileHit) {
+        if (slot < 0 || slot >= a.C) {
+            if (threadIdx.x == 0) atomicOr(&a.ctrl[kWordFlags], (uint32_t)SPICE_FLAG_BAD_SLOT);
+            return false;
+        }
+        j.w = kUp ? a.w13_pool + (size_t)slot * 2 * I * d : a.w2_pool + (size_t)slot * d * I;
+        j.w_bytes = (uint32_t)(kUp ? 2 : 1) * (uint32_t)I * (uint32_t)d * 2u;
+        j.kdim = kUp ? d : I;
+        j.nfeat = kUp ? I : d;
+        j.up_off = I;
+        j.row0 = nn * feat;
+    } else {
+        j.w = (kUp ? a.lore_A : a.lore_B) + (size_t)e * a.r * d;
+        j.w_bytes = (uint32_t)a.r * (uint32_t)d * 2u;
+        j.kdim = kUp ? d : a.r;
+        j.nfeat = kUp ? a.r : d;
+        j.up_off = C::kUpFeat;  // BM consecutive rows of A
+        j.row0 = nn * C::BM;
+    }
+    j.k1 = (j.kdim + kBK - 1) / kBK;
     return true;
 }
 
 // Byte offset of 16-byte chunk c of staged row r inside an operand tile.
-// XOR swizzle of the 16-byte chunks of a staged row.  Measured on gfx950 with the
-// LDS bank-conflict counter: 128-byte rows swizzled by (r >> 1) & 7 read 16 rows x 4
-// chunks per ds_read_b128 and write 8 chunks per row without conflicts, where padded
-// rows, 64-byte rows and unswizzled rows do not.
 __device__ __forceinline__ uint32_t lds_off(int r, int c) {
-    const int sw = kBK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3);
-    return (uint32_t)(r * kRowBytes + ((c ^ sw) << 4));
+    return (uint32_t)(r * 128 + ((c ^ ((r >> 1) & 7)) << 4));
 }
 
-// 16 bytes from this lane's global address to LDS byte lds + 16 * lane, for an lds address
-// uniform over the wave (global_load_lds_dwordx4; counted by vmcnt, not lgkmcnt).  Device
-// pass only: the host pass of a kernel naming this target builtin would lose its launch stub.
-__device__ __forceinline__ void load_lds16(const void* g, void* lds) {
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t raw_buffer(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kRawBufferWord3);
+}
+
+// 16 bytes from offset off of a buffer to LDS byte lds + 16 * lane, lds uniform over the wave
+// (counted by vmcnt, not lgkmcnt; an offset past the buffer writes zeros).  Device pass only:
+// the host pass of a kernel naming this target builtin would lose its launch stub.
+__device__ __forceinline__ void load_lds16(rsrc_t b, uint32_t off, unsigned char* lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_global_load_lds(g, lds, 16, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (__attribute__((address_space(3))) void*)lds, 16, (int)off, 0, 0, 0);
 #endif
 }
 
-template <bool kUp>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kWavesPerEU))) void expert_gemm_kernel(
-    GemmArgs a) {
-    extern __shared__ __align__(16) unsigned char s_lds[];
-    __shared__ int s_scan[4];
-    TileJob j;
-    if (!resolve<kUp>(a, xcd_tile(blockIdx.x, gridDim.x), j, s_scan)) return;
+// s_waitcnt with vmcnt(n) lgkmcnt(0), then the block's barrier: no wait for loads to LDS
+// beyond those the caller names (a __syncthreads would drain them all).
+template <int n>
+__device__ __forceinline__ void wait_and_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | 0x70);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // wave's feature half and token lane group: token sub-tile t of the wave holds the tile's
-    // rows kTStride t + 16 wt .. + 15, so a ragged last tile spreads over the SIMDs
-    const int wf = w & 1, wt = __builtin_amdgcn_readfirstlane(w >> 1);
+// Fragments of one 32-k step: RF weight sub-tiles and the NL live token sub-tiles.
+template <class C, int NL>
+struct Frags {
+    u32x4_t a[C::RF], b[NL];
+};
+
+// The bf16 main loop of one tile with NL live token sub-tiles in this wave (NL = 0: the wave
+// only loads and keeps the barriers).
+template <class C, bool kUp, int NL, class Load>
+__device__ __forceinline__ void product(unsigned char* s_lds, int nk, uint32_t fbase, uint32_t tbase, Load load,
+                                        f32x4_t (&acc)[C::RF][C::RT]) {
+    constexpr int N1 = NL > 0 ? NL : 1;
+    constexpr int kLoads = (C::S - 2) * (C::kWLoads + C::kXLoads);  // stages in flight past the next one
+    auto read = [&](int buf, uint32_t kx, Frags<C, N1>& f) {
+        if constexpr (NL > 0) {
+            const unsigned char* base = s_lds + buf * C::kStage;
+#pragma unroll
+            for (int t = 0; t < NL; ++t)
+                f.b[t] = *reinterpret_cast<const u32x4_t*>(base + ((tbase + t * C::kTStride * 128) ^ kx));
+#pragma unroll
+            for (int s = 0; s < C::RF; ++s) {
+                const int row = kUp ? (s % (C::RF / 2)) * 16 + (s / (C::RF / 2)) * C::kUpFeat : s * 16;
+                f.a[s] = *reinterpret_cast<const u32x4_t*>(base + ((fbase + row * 128) ^ kx));
+            }
+        }
+    };
+    auto mma = [&](const Frags<C, N1>& f) {
+        if constexpr (NL > 0) {
+            __builtin_amdgcn_s_setprio(1);  // favour the wave that is issuing MFMAs
+#pragma unroll
+            for (int t = 0; t < NL; ++t)
+#pragma unroll
+                for (int s = 0; s < C::RF; ++s)
+                    acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f.a[s]),
+                                                                        __builtin_bit_cast(bf16x8_t, f.b[t]),
+                                                                        acc[s][t], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+        }
+    };
+    wait_and_barrier<kLoads + C::kWLoads + C::kXLoads>();  // stage 0 of the S in flight has landed
+    Frags<C, N1> f0, f1;
+    read(0, 0u, f0);
+    int buf = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        read(buf, 64u, f1);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        // stage kt + 1 has landed and every wave has read all of stage kt
+        wait_and_barrier<kLoads>();
+        load(buf, kt + C::S);
+        buf = buf + 1 == C::S ? 0 : buf + 1;
+        read(buf, 0u, f0);  // past the last stage: zeros, unused
+        __builtin_amdgcn_sched_barrier(0);
+        mma(f1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_waitcnt(0x70);  // no load to LDS outlives the block
+}
+
+// Row of x of a tile row: the token itself (shared block) or that of slot s of the bucket
+// (row 0 and a flag for a slot out of range).
+__device__ __forceinline__ int token_row(const GemmArgs& a, const TileJob& j, int s) {
+    if (j.kind == kTileShared) return s;
+    if (s < 0 || s >= a.T * a.K) {
+        atomicOr(&a.ctrl[kWordFlags], (uint32_t)SPICE_FLAG_BAD_INDEX);
+        return 0;
+    }
+    return s / a.K;
+}
+
+// D = U B_e^T of a LORE tile: BM rows of B_e x BT bucket entries, contraction r.  fp32 MFMAs
+// (16x16x4), so that U keeps its 32 bits; operands straight from L2, whose reuse is within the
+// block.  A 16-k step gives each lane 4 consecutive k of its row (quad), and MFMA i takes
+// element i of every lane.  Rows past d and entries past the bucket read the last one.
+template <class C>
+__device__ __forceinline__ void lore_down(const GemmArgs& a, const TileJob& j) {
+    const int lane = threadIdx.x & 63, m = lane & 15, quad = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wf = w % C::WF, wt = w / C::WF;
+    const int nlive = min(C::RT, max(0, (j.ntok - j.tok0 - 16 * wt + C::kTStride - 1) / C::kTStride));
+    const uint16_t* B = static_cast<const uint16_t*>(j.w);
+    f32x4_t acc[C::RF][C::RT];
+#pragma unroll
+    for (int s = 0; s < C::RF; ++s)
+#pragma unroll
+        for (int t = 0; t < C::RT; ++t) acc[s][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const uint16_t* brow[C::RF];
+    const float* urow[C::RT];
+#pragma unroll
+    for (int s = 0; s < C::RF; ++s)
+        brow[s] = B + (size_t)min(j.row0 + wf * (C::BM / C::WF) + s * 16 + m, a.d - 1) * a.r;
+#pragma unroll
+    for (int t = 0; t < C::RT; ++t)
+        urow[t] = a.u + (size_t)(j.start + min(j.tok0 + t * C::kTStride + wt * 16 + m, j.ntok - 1)) * a.r;
+    for (int k0 = 0; k0 < a.r; k0 += 16) {
+        const int k = k0 + quad * 4;
+        const bool in = k < a.r;  // r is a multiple of 8
+        float av[C::RF][4];
+        f32x4_t bv[C::RT];
+#pragma unroll
+        for (int s = 0; s < C::RF; ++s) {
+            uint2 v = {0u, 0u};
+            if (in) v = *reinterpret_cast<const uint2*>(brow[s] + k);
+            av[s][0] = __uint_as_float(v.x << 16);
+            av[s][1] = __uint_as_float(v.x & 0xFFFF0000u);
+            av[s][2] = __uint_as_float(v.y << 16);
+            av[s][3] = __uint_as_float(v.y & 0xFFFF0000u);
+        }
+#pragma unroll
+        for (int t = 0; t < C::RT; ++t) {
+            bv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (in && t < nlive) bv[t] = *reinterpret_cast<const f32x4_t*>(urow[t] + k);
+        }
+#pragma unroll
+        for (int t = 0; t < C::RT; ++t) {
+            if (t >= nlive) continue;
+#pragma unroll
+            for (int s = 0; s < C::RF; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][i], bv[t][i], acc[s][t], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < C::RT; ++t) {
+        const int pos = j.tok0 + t * C::kTStride + wt * 16 + m;
+        if (pos >= j.ntok) continue;
+        float* dst = a.y_slots + (size_t)(j.start + pos) * a.d;
+#pragma unroll
+        for (int s = 0; s < C::RF; ++s) {
+            const int f = j.row0 + wf * (C::BM / C::WF) + s * 16 + quad * 4;
+            if (f < a.d) *reinterpret_cast<f32x4_t*>(dst + f) = acc[s][t];
+        }
+    }
+}
+
+template <bool kUp, class C>
+__global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::W))) void expert_gemm_kernel(GemmArgs a) {
+    extern __shared__ __align__(16) unsigned char s_lds[];
+    TileJob j;
+    if (!resolve<kUp, C>(a, xcd_tile(blockIdx.x, gridDim.x, C::kXcdBlocks), j)) return;
+    if constexpr (!kUp) {
+        if (j.kind == kTileLore) {
+            lore_down<C>(a, j);
+            return;
+        }
+    }
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // wave's feature part and token lane group
+    const int wf = w % C::WF, wt = w / C::WF;
     const int m = lane & 15, quad = lane >> 4;
 
-    // Staging: waves 0-3 (one per SIMD) issue all of a stage's loads, so waves 4-7 never wait
-    // behind a queue of loads and keep their SIMD's MFMAs going at the start of a stage.  A
-    // wave's direct load (global_load_lds_dwordx4) writes 64 x 16 bytes to consecutive LDS:
-    // 8 staged rows of 8 chunks.  Lane l fills LDS chunk l % 8 of row r0 = tid / kCPR (+
-    // kRowStep i), which holds the row's chunk (l % 8) ^ swizzle(row), so that is the chunk
-    // it fetches.  Weight rows step by a constant, so one 32-bit element offset (from the
-    // group's uniform base pointer) and uniform deltas address them; token rows are gathered.
-    const int r0 = (tid % kLoaders) / kCPR;
-    const bool loader = tid < kLoaders;
-    static_assert(kRowStep % 16 == 0 && kUpFeat % kRowStep == 0, "staging rows keep their swizzle");
-    static_assert(kThreads % 64 == 0 && 64 % kCPR == 0, "a wave stages whole rows");
-    const int c16 = (int)((uint32_t)(lds_off(r0, tid % kCPR) % kRowBytes) >> 4);  // the chunk landing at this lane's slot
-    const uint32_t woff0 = (uint32_t)(j.wrow0 + r0) * (uint32_t)j.kdim + c16 * 8;
-    auto wrow_delta = [&](int i) -> uint32_t {  // rows between chunk 0 and chunk i (uniform)
-        const int r = kRowStep * i;
-        if (kUp && r >= kUpFeat) return (uint32_t)(j.up_off + r - kUpFeat) * (uint32_t)j.kdim;
-        return (uint32_t)r * (uint32_t)j.kdim;
+    // Staging: a loader wave's load writes 64 x 16 bytes to consecutive LDS, 8 staged rows of 8
+    // chunks.  Lane l fills LDS chunk l % 8 of row r0 = tid / 8 (+ kRowStep i), which holds the
+    // row's chunk (l % 8) ^ swizzle(row), so that is the chunk it fetches.
+    const int r0 = tid / 8;
+    const bool loader = C::kLoaders == C::kThreads || tid < C::kLoaders;
+    const int c16 = (int)((lds_off(r0, tid & 7) & 127u) >> 4);
+    const rsrc_t wbuf = raw_buffer(j.w, j.w_bytes);
+    const int S = j.kind == kTileShared ? a.T : a.T * a.K;  // rows of the activations behind the tile
+    const rsrc_t xbuf = kUp ? raw_buffer(a.x, (uint32_t)a.T * (uint32_t)a.d * 2u)
+                            : raw_buffer(j.kind == kTileShared ? a.hs : a.h,
+                                         (uint32_t)S * (uint32_t)((j.kdim + kBK - 1) / kBK) * (kBK * 2u));
+    const uint32_t wstep = (uint32_t)j.kdim * 2u;
+    const uint32_t woff0 = (uint32_t)(j.row0 + r0) * wstep + c16 * 16;
+    const uint32_t xstep = kUp ? 128u : (uint32_t)S * 128u;  // bytes from one stage to the next
+    const int klim = j.kdim - c16 * 8;  // the lane's chunk of stage kt is in the row while 64 kt < klim
+    const int nk = j.k1 - j.k0;
+    // Weight rows whose stride is a multiple of 2 KiB start on a few memory channels only, and
+    // tiles that march through k together queue there: each weight tile starts its k order at
+    // another stage (d = 2048, T = 192: 235 -> 217 us a call; at d = 3584, whose rows spread by
+    // themselves, the lost sharing in L2 costs 1-2 %).
+    const int rot = wstep % 2048 == 0 ? (int)((uint32_t)(j.row0 / C::kUpFeat) * 5u % (uint32_t)nk) : 0;
+    // stage kt of the tile's nk; past the last one, a stage past the row
+    auto stage_k = [&](int kt) {
+        return kt >= nk ? 0x1000000 : j.k0 + (kt + rot >= nk ? kt + rot - nk : kt + rot);
     };
-    // element offsets of a loader's token rows, kept in LDS (each loader reads back only its
-    // own) rather than in registers, which the accumulators and fragments fill
-    __shared__ uint32_t s_xoff[kXChunks][kLoaders];
-    if (loader) {
-#pragma unroll
-        for (int i = 0; i < kXChunks; ++i) {
-            // token rows past the group's end read its last row; their outputs are dropped
-            const int pos = min(j.tok0 + r0 + kRowStep * i, j.ntok - 1);
-            int row;
-            if (j.shared) {
-                row = pos;
-            } else if (j.gather) {
-                const int s = a.perm[j.start + pos];
-                if (s < 0 || s >= a.T * a.K) {
-                    atomicOr(&a.ctrl[kWordFlags], (uint32_t)SPICE_FLAG_BAD_INDEX);
-                    row = 0;
-                } else {
-                    row = s / a.K;
-                }
-            } else {
-                row = j.start + pos;
-            }
-            s_xoff[i][tid] = (uint32_t)row * (uint32_t)j.ld + c16 * 8;
-        }
-    }
-    const uint16_t* __restrict__ wbase = j.w;
-    const uint16_t* __restrict__ xbase = j.act;
-
-    f32x4_t acc[8][kTS];
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int t = 0; t < kTS; ++t) acc[s][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    // LDS addresses.  The swizzle of row r depends on (r >> 1) & 7, which steps of 16
-    // rows leave unchanged, so every sub-tile / staging chunk is a constant offset from
-    // one base.  Fragments of k-step 0; with kBK = 64, k-step 1 reads chunk c ^ 4, i.e.
-    // the address with bit 6 flipped.  Weights (A): for `up` the wave's feature
-    // sub-tiles 0..3 are W1 rows wf*64 + 16 s and 4..7 the W3 rows kUpFeat + the same.
-    const uint32_t fbase = lds_off(kUp ? wf * 64 + m : wf * 128 + m, quad);
-    const uint32_t tbase = kWTile + lds_off(wt * 16 + m, quad);
-    // token sub-tiles of this wave with a live row; the others issue no MFMA
-    const int nlive = min(kTS, max(0, (j.ntok - j.tok0 - 16 * wt + kTStride - 1) / kTStride));
-    auto frag_row = [](int s) { return kUp ? (s & 3) * 16 + (s >> 2) * kUpFeat : s * 16; };
-
-    const int nk = j.kdim / kBK;
-    // Stage kt goes straight from global memory into LDS buffer buf: chunk i of this loader
-    // lane lands in its wave's 1 KiB run of the chunk's rows (lane l at byte 16 l).
-    auto load = [&](int buf, int kt) {  // loaders only
+    auto load_w = [&](int buf, int kt) {
         if (!loader) return;
-        const uint32_t o = (uint32_t)kt * kBK, ox = (uint32_t)kt * j.kst;
-        unsigned char* run = s_lds + buf * kStageLds + (w & 3) * 64 * 16;
+        unsigned char* run = s_lds + buf * C::kStage + w * 1024;
+        kt = stage_k(kt);
+        const bool in = kt * kBK < klim;
 #pragma unroll
-        for (int i = 0; i < kWChunks; ++i)
-            load_lds16(wbase + woff0 + wrow_delta(i) + o, run + i * kRowStep * kRowBytes);
-#pragma unroll
-        for (int i = 0; i < kXChunks; ++i)
-            load_lds16(xbase + s_xoff[i][tid] + ox, run + kWTile + i * kRowStep * kRowBytes);
-    };
-    auto compute = [&](int buf) {
-        const unsigned char* base = s_lds + buf * kStageLds;
-        // the fragments of both k-steps are requested before the first MFMA, so the LDS
-        // latency is paid once per stage
-        u32x4_t bfr[kBK / 32][kTS], afr[kBK / 32][8];
-#pragma unroll
-        for (int ks = 0; ks < kBK / 32; ++ks) {
-            const uint32_t kx = ks ? 64u : 0u;
-#pragma unroll
-            for (int t = 0; t < kTS; ++t)
-                bfr[ks][t] = *reinterpret_cast<const u32x4_t*>(base + ((tbase + t * kTStride * kRowBytes) ^ kx));
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                afr[ks][s] = *reinterpret_cast<const u32x4_t*>(base + ((fbase + frag_row(s) * kRowBytes) ^ kx));
+        for (int i = 0; i < C::kWLoads; ++i) {
+            const int r = C::kRowStep * i;
+            const uint32_t delta = (uint32_t)(kUp && r >= C::kUpFeat ? j.up_off + r - C::kUpFeat : r) * wstep;
+            load_lds16(wbuf, in ? woff0 + delta + (uint32_t)kt * 128u : kOutOfRange, run + i * C::kRowStep * 128);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(1);  // favour the wave that is issuing MFMAs
-#pragma unroll
-        for (int ks = 0; ks < kBK / 32; ++ks)
-#pragma unroll
-            for (int t = 0; t < kTS; ++t) {
-                if (t >= nlive) continue;  // no live token in this sub-tile
-#pragma unroll
-                for (int s = 0; s < 8; ++s)
-                    acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, afr[ks][s]),
-                                                                        __builtin_bit_cast(bf16x8_t, bfr[ks][t]),
-                                                                        acc[s][t], 0, 0, 0);
-            }
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
     };
+    uint32_t xoff[C::kXLoads];
+    auto load_x = [&](int buf, int kt) {
+        if (!loader) return;
+        unsigned char* run = s_lds + buf * C::kStage + w * 1024 + C::kWTile;
+        kt = stage_k(kt);
+        const bool in = kt * kBK < klim;
+#pragma unroll
+        for (int i = 0; i < C::kXLoads; ++i)
+            load_lds16(xbuf, in && xoff[i] != kOutOfRange ? xoff[i] + (uint32_t)kt * xstep : kOutOfRange,
+                       run + i * C::kRowStep * 128);
+    };
+    auto load = [&](int buf, int kt) {
+        load_w(buf, kt);
+        load_x(buf, kt);
+    };
+    // the slot ids of the tile's rows, the weights of stage 0, then (once the ids are there) its
+    // token rows and the other stages of the ring
+    int sid[C::kXLoads];
+#pragma unroll
+    for (int i = 0; i < C::kXLoads; ++i) {
+        const int pos = j.tok0 + r0 + C::kRowStep * i;
+        sid[i] = -1;
+        if (loader && pos < j.ntok) sid[i] = (!kUp || j.kind == kTileShared) ? j.start + pos : a.perm[j.start + pos];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < C::kXLoads; ++i) {
+        const int pos = j.tok0 + r0 + C::kRowStep * i;
+        xoff[i] = kOutOfRange;
+        if (loader && pos < j.ntok)
+            xoff[i] = kUp ? (uint32_t)token_row(a, j, sid[i]) * (uint32_t)a.d * 2u + c16 * 16
+                          : (uint32_t)sid[i] * 128u + c16 * 16;
+    }
+    load_x(0, 0);
+#pragma unroll
+    for (int s = 1; s < C::S; ++s) load(s, s);
 
-    // The loads of stage kt + 1 run under the MFMAs of stage kt; its LDS buffer was last
-    // read in stage kt - 1, which every wave finished before the previous barrier.
-    load(0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's direct loads have landed
-        __syncthreads();
-        if (kt + 1 < nk) load((kt + 1) & 1, kt + 1);
-        compute(kt & 1);
+    f32x4_t acc[C::RF][C::RT];
+#pragma unroll
+    for (int s = 0; s < C::RF; ++s)
+#pragma unroll
+        for (int t = 0; t < C::RT; ++t) acc[s][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // LDS addresses of the fragments of k-step 0 (k-step 1 reads chunk c ^ 4: bit 6 flipped).
+    // The swizzle of row r depends on (r >> 1) & 7, which steps of 16 rows leave unchanged.
+    const int frow0 = wf * ((kUp ? C::kUpFeat : C::BM) / C::WF);
+    const uint32_t fbase = lds_off(frow0 + m, quad);
+    const uint32_t tbase = C::kWTile + lds_off(wt * 16 + m, quad);
+    // token sub-tiles of this wave with a live row
+    const int nlive = min(C::RT, max(0, (j.ntok - j.tok0 - 16 * wt + C::kTStride - 1) / C::kTStride));
+    static_assert(C::RT == 2 || C::RT == 4, "token sub-tiles per wave");
+    if (nlive == C::RT) product<C, kUp, C::RT>(s_lds, nk, fbase, tbase, load, acc);
+    else if (nlive == 0) product<C, kUp, 0>(s_lds, nk, fbase, tbase, load, acc);
+    else if (nlive == 1) product<C, kUp, 1>(s_lds, nk, fbase, tbase, load, acc);
+    else if constexpr (C::RT > 2) {
+        if (nlive == 2) product<C, kUp, 2>(s_lds, nk, fbase, tbase, load, acc);
+        else product<C, kUp, 3>(s_lds, nk, fbase, tbase, load, acc);
     }
 
-    // Epilogue: lane holds features 4*quad .. +3 of sub-tile s for token m of sub-tile t.
+    // Epilogue: lane holds features 4 quad .. + 3 of sub-tile s for token m of sub-tile t.
 #pragma unroll
-    for (int t = 0; t < kTS; ++t) {
-        const int pos = j.tok0 + t * kTStride + wt * 16 + m;
+    for (int t = 0; t < C::RT; ++t) {
+        const int pos = j.tok0 + t * C::kTStride + wt * 16 + m;
         if (pos >= j.ntok) continue;
-        if (kUp) {
-            // intermediates are k-blocked: element (row, f) at ((f / kBK) * rows + row) * kBK + f % kBK,
-            // so a down-projection stage reads its token rows as one contiguous block
-            uint16_t* dst = j.shared ? a.hs + (size_t)pos * kBK : a.h + (size_t)(j.start + pos) * kBK;
-            const size_t fstride = (size_t)(j.shared ? a.T : a.T * a.K) * kBK;
+        if constexpr (kUp) {
+            if (j.kind == kTileLore) {
+                float* dst = a.u + (size_t)(j.start + pos) * a.r;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const f32x4_t g = acc[s][t], u = acc[s + 4][t];
-                const int f = j.feat0 + wf * 64 + s * 16 + quad * 4;
+                for (int s = 0; s < C::RF; ++s) {
+                    const int q = j.row0 + frow0 + (s % (C::RF / 2)) * 16 + (s / (C::RF / 2)) * C::kUpFeat + quad * 4;
+                    if (q < a.r) *reinterpret_cast<f32x4_t*>(dst + q) = acc[s][t];
+                }
+                continue;
+            }
+            // intermediates are k-blocked: element (row, f) at ((f / 64) * rows + row) * 64 + f % 64,
+            // so a down-projection stage reads its token rows as one contiguous block
+            uint16_t* dst = (j.kind == kTileShared ? a.hs : a.h) + (size_t)(j.start + pos) * kBK;
+            const size_t fstride = (size_t)S * kBK;
+#pragma unroll
+            for (int s = 0; s < C::RF / 2; ++s) {
+                const f32x4_t g = acc[s][t], u = acc[s + C::RF / 2][t];
+                const int f = j.row0 + frow0 + s * 16 + quad * 4;
                 uint2 p;
                 p.x = bf16_rne(silu(g.x) * u.x) | (bf16_rne(silu(g.y) * u.y) << 16);
                 p.y = bf16_rne(silu(g.z) * u.z) | (bf16_rne(silu(g.w) * u.w) << 16);
-                *reinterpret_cast<uint2*>(dst + (size_t)(f / kBK) * fstride + (f % kBK)) = p;
+                if (f < j.nfeat) *reinterpret_cast<uint2*>(dst + (size_t)(f / kBK) * fstride + (f % kBK)) = p;
             }
         } else {
-            float* dst = j.shared ? a.y_shared + (size_t)pos * a.d : a.y_slots + (size_t)(j.start + pos) * a.d;
-            const float gs = (j.shared && a.sgate) ? a.sgate[pos] : 1.0f;  // gated shared block
+            const bool shared = j.kind == kTileShared, split = shared && a.parts > 1;
+            float* dst = split ? a.part + ((size_t)j.part * a.T + pos) * a.d
+                               : (shared ? a.y_shared : a.y_slots) + (size_t)(j.start + pos) * a.d;
+            const float gs = (shared && a.sgate && !split) ? a.sgate[pos] : 1.0f;  // gated shared block
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const int f = j.feat0 + wf * 128 + s * 16 + quad * 4;
-                *reinterpret_cast<f32x4_t*>(dst + f) = acc[s][t] * gs;
+            for (int s = 0; s < C::RF; ++s) {
+                const int f = j.row0 + frow0 + s * 16 + quad * 4;
+                if (f < a.d) *reinterpret_cast<f32x4_t*>(dst + f) = acc[s][t] * gs;
             }
         }
     }
 }
 
+// y_shared = the sum of the shared block's partial results, in order, times the gate: 4
+// features of one token per thread.
+__global__ __launch_bounds__(256) void shared_sum_kernel(int T, int d, int parts, const float* part, const float* sgate,
+                                                         float* y) {
+    const int f = (blockIdx.x * 256 + threadIdx.x) * 4, t = blockIdx.y;
+    if (f >= d) return;
+    const size_t at = (size_t)t * d + f, step = (size_t)T * d;
+    f32x4_t v[kMaxSharedParts];
+#pragma unroll
+    for (int p = 0; p < kMaxSharedParts; ++p)
+        if (p < parts) v[p] = *reinterpret_cast<const f32x4_t*>(part + p * step + at);
+    f32x4_t sum = v[0];
+#pragma unroll
+    for (int p = 1; p < kMaxSharedParts; ++p)
+        if (p < parts) sum += v[p];
+    if (sgate) sum *= sgate[t];
+    *reinterpret_cast<f32x4_t*>(y + at) = sum;
+}
+
 // Super-tile of the shared block: sn weight tiles x sm token tiles with sn | nt and
-// sm | mt, at most one XCD round of blocks, as square as possible (the bytes a group
+// sm | mt, at most one XCD's resident blocks, as square as possible (the bytes a group
 // fetches per stage are proportional to sn + sm).
-void super_shape(int mt, int nt, int* out) {
+void super_shape(int mt, int nt, int most, int* out) {
     int best_n = 1, best_m = 1, best_score = -1;
-    for (int sm = 1; sm <= mt && sm <= kXcdBlocks; ++sm) {
+    for (int sm = 1; sm <= mt && sm <= most; ++sm) {
         if (mt % sm) continue;
-        for (int sn = 1; sn <= nt && sn * sm <= kXcdBlocks; ++sn) {
+        for (int sn = 1; sn <= nt && sn * sm <= most; ++sn) {
             if (nt % sn) continue;
             // more blocks per group first, then fewer distinct tiles per block
             const int score = sn * sm * 64 - (sn + sm);
@@ -400,18 +596,48 @@ void super_shape(int mt, int nt, int* out) {
     out[1] = best_m;
 }
 
+template <class C>
+hipError_t launch_shape(GemmArgs a, bool lore, hipStream_t s) {
+    const long long TK = (long long)a.T * a.K, mt_sh = (a.T + C::BT - 1) / C::BT;
+    auto tiles = [](int n, int per) { return (long long)(n + per - 1) / per; };
+    // upper bounds of the tile counts: sum_e ceil(n_e / BT) <= slots / BT + buckets, the slots of
+    // both classes together at most T K; blocks past the live tiles exit
+    const long long hit_b = a.do_hit ? std::min<long long>(std::min(a.N, a.C), TK) : 0;
+    const long long lore_b = lore ? std::min<long long>(a.N, TK) : 0;
+    auto bound = [&](long long nt_sh, long long nt_e, long long nt_l, int parts) {
+        return (a.Is > 0 ? mt_sh * nt_sh * parts : 0) + TK / C::BT * std::max(a.do_hit ? nt_e : 0, lore ? nt_l : 0) +
+               hit_b * nt_e + lore_b * nt_l;
+    };
+    const long long up = bound(tiles(a.Is, C::kUpFeat), tiles(a.I, C::kUpFeat), tiles(a.r, C::BM), 1);
+    const long long dn = bound(tiles(a.d, C::BM), tiles(a.d, C::BM), tiles(a.d, C::BM), a.parts);
+    if (up == 0) return hipSuccess;
+    if (up > 0x7FFFFFFFll || dn > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    if (a.Is > 0) {
+        super_shape((int)mt_sh, (int)tiles(a.Is, C::kUpFeat), C::kXcdBlocks, a.super_up);
+        super_shape((int)mt_sh, (int)tiles(a.d, C::BM), C::kXcdBlocks, a.super_dn);
+    }
+    const size_t lds = C::S * C::kStage;
+    hipLaunchKernelGGL((expert_gemm_kernel<true, C>), dim3((unsigned)up), dim3(C::kThreads), lds, s, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((expert_gemm_kernel<false, C>), dim3((unsigned)dn), dim3(C::kThreads), lds, s, a);
+    if (a.Is > 0 && a.parts > 1)
+        hipLaunchKernelGGL(shared_sum_kernel, dim3((unsigned)((a.d / 4 + 255) / 256), (unsigned)a.T), dim3(256), 0, s, a.T,
+                           a.d, a.parts, a.part, a.sgate, a.y_shared);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool expert_gemm_applies(const FfnArgs& a) {
-    if (a.dtype != SPICE_BF16 || a.T < kGemmMinTokens || a.d % kBM || a.d % kBK || a.I % kUpFeat ||
-        a.Is % kUpFeat || a.I % kBK || a.Is % kBK)
+    if (a.dtype != SPICE_BF16 || a.T < gemm_min_tokens(a.d, a.Is)) return false;
+    // offsets inside one operand are 32-bit
+    auto fits = [](long long rows, long long cols) { return rows * ((cols + kBK - 1) / kBK * kBK) * 2 <= kMaxBuffer; };
+    const long long TK = (long long)a.T * a.K;
+    if (!fits(a.T, a.d) || !fits(TK, a.I) || !fits(a.T, a.Is) || !fits(2ll * a.I, a.d) || !fits(2ll * a.Is, a.d) ||
+        !fits(a.d, a.I) || !fits(a.d, a.Is))
         return false;
-    // element offsets inside one operand are 32-bit
-    const long long lim = 0x7FFFFFFFll;
-    if ((long long)a.I * a.T * a.K > lim || (long long)a.Is * a.T > lim || (long long)a.d * a.T * a.K > lim ||
-        2ll * a.I * a.d > lim || 2ll * a.Is * a.d > lim)
-        return false;
-    // the double-buffered tiles need more LDS than the 64 KiB every AMD GPU offers
+    // the staged tiles need more LDS than the 64 KiB every AMD GPU offers
     static int lds_per_block[64] = {0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
@@ -420,45 +646,39 @@ bool expert_gemm_applies(const FfnArgs& a) {
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return false;
         lds_per_block[dev] = v;
     }
-    return lds_per_block[dev] >= 2 * kStageLds;
+    return lds_per_block[dev] >= std::max(Big::S * Big::kStage, Small::S * Small::kStage);
 }
 
 hipError_t launch_expert_gemm(const FfnArgs& f, bool hit, bool shared, hipStream_t s) {
+    const bool lore = (f.groups & kDoLore) != 0 && f.r > 0;
     GemmArgs a{};
     a.T = f.T; a.d = f.d; a.N = f.N; a.K = f.K; a.C = f.C; a.I = f.I; a.Is = shared ? f.Is : 0;
-    a.ldh = f.ldh; a.ldhs = f.ldhs;
+    a.r = lore ? f.r : 0;
+    a.do_hit = hit ? 1 : 0;
     a.x = static_cast<const uint16_t*>(f.x);
     a.perm = f.perm;
-    a.offsets = f.offsets;  // the HIT class comes first
+    a.offsets = f.offsets;
     a.resident_slot = f.resident_slot;
     a.w13_pool = static_cast<const uint16_t*>(f.w13_pool);
     a.w2_pool = static_cast<const uint16_t*>(f.w2_pool);
     a.w13s = static_cast<const uint16_t*>(f.w13s);
     a.w2s = static_cast<const uint16_t*>(f.w2s);
+    a.lore_A = static_cast<const uint16_t*>(f.lore_A);
+    a.lore_B = static_cast<const uint16_t*>(f.lore_B);
+    a.u = f.u;
     a.h = static_cast<uint16_t*>(f.h);
     a.hs = static_cast<uint16_t*>(f.hs);
     a.y_slots = f.y_slots;
     a.y_shared = f.y_shared;
     a.sgate = f.sgate;
     a.ctrl = f.ctrl;
-    if (!hit) a.N = 0;  // no expert tiles
-    // upper bound of the tile count: sum_e ceil(n_e / kBT) <= T*K / kBT + min(N, C)
-    const long long mt_hit = hit ? (long long)a.T * a.K / kBT + std::min(a.N, a.C) : 0;
-    const long long mt_sh = (a.T + kBT - 1) / kBT;
-    const long long up_tiles = (a.Is > 0 ? mt_sh * (a.Is / kUpFeat) : 0) + mt_hit * (a.I / kUpFeat);
-    const long long dn_tiles = (a.Is > 0 ? mt_sh * (a.d / kBM) : 0) + mt_hit * (a.d / kBM);
-    if (up_tiles == 0) return hipSuccess;
-    if (up_tiles > 0x7FFFFFFFll || dn_tiles > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    if (a.Is > 0) {
-        super_shape((int)mt_sh, a.Is / kUpFeat, a.super_up);
-        super_shape((int)mt_sh, a.d / kBM, a.super_dn);
+    a.part = f.part;
+    a.parts = a.Is > 0 && f.part ? gemm_shared_parts(f.T, f.d, f.N, f.K, f.C, f.I, f.Is) : 1;
+    switch (gemm_shape(f.T, f.N, f.K)) {
+        case kGemmBig: return launch_shape<Big>(a, lore, s);
+        case kGemmWide: return launch_shape<Wide>(a, lore, s);
+        default: return launch_shape<Small>(a, lore, s);
     }
-    const size_t lds = 2 * kStageLds;
-    hipLaunchKernelGGL(expert_gemm_kernel<true>, dim3((unsigned)up_tiles), dim3(kThreads), lds, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(expert_gemm_kernel<false>, dim3((unsigned)dn_tiles), dim3(kThreads), lds, s, a);
-    return hipGetLastError();
 }
 
 }  // namespace spice

@@ -56,7 +56,7 @@ extern "C" spice_status_t moe_layer_gpu_noalloc(
     float* y_slots, float* y_shared, const spice_host_out_t* host_out, const float* resid, void* out,
     spice_stream_t stream) {
     try {
-        const size_t need = spice_workspace_bytes(cfg, T);
+        const size_t need = spice_workspace_bytes(cfg, T) ? spice::ws_layout(*cfg, T).base : 0;
         if (need == 0) {  // an invalid cfg or T: the call below reports which
             return moe_layer_gpu(cfg, T, x, w_gate, logit_bias, resident_slot, conf, w13_pool, w2_pool, w13_shared,
                                  w2_shared, w_shared_gate, lore_A, lore_B, logits, topk_idx, topk_w, slot_class,

@@ -73,7 +73,7 @@ spice_status_t check_tokens(const spice_moe_cfg_t& c, int32_t T) {
 
 spice_status_t check_ws(const spice_moe_cfg_t& c, int32_t T, const void* ws, size_t ws_bytes) {
     if (!ws) return fail(SPICE_ERR_INVALID, "workspace is NULL");
-    const size_t need = spice::ws_layout(c, T).total;
+    const size_t need = spice::ws_layout(c, T).base;
     if (ws_bytes < need)
         return fail(SPICE_ERR_WORKSPACE, "workspace has " + std::to_string(ws_bytes) + " bytes, needs " +
                                              std::to_string(need));
@@ -168,6 +168,10 @@ WsLayout ws_layout(const spice_moe_cfg_t& c, int32_t T) {
     L.hs = off;     off += align256(t * ((size_t)c.shared_inter + kHPad) * es);
     L.u = off;      off += align256(slots * (size_t)c.lore_rank * sizeof(float));
     L.sgate = off;  off += align256(t * sizeof(float));
+    L.base = off;
+    const int parts = c.dtype == SPICE_BF16 ? gemm_shared_parts(T, c.d, c.n_experts, c.top_k, c.n_slots, c.inter,
+                                                                c.shared_inter) : 1;
+    L.part = off;   off += parts > 1 ? align256((size_t)parts * t * c.d * sizeof(float)) : 0;
     L.total = off;
     return L;
 }
@@ -322,6 +326,7 @@ spice_status_t prep_ffn(const spice_moe_cfg_t* cfg, int32_t T, const void* x, co
     a.w13_pool = w13_pool; a.w2_pool = w2_pool; a.w13s = w13_shared; a.w2s = w2_shared;
     a.lore_A = lore_A; a.lore_B = lore_B; a.y_slots = y_slots; a.y_shared = y_shared;
     a.h = wsb + L.h; a.hs = wsb + L.hs; a.u = reinterpret_cast<float*>(wsb + L.u);
+    a.part = L.total > L.base && ws_bytes >= L.total ? reinterpret_cast<float*>(wsb + L.part) : nullptr;
     a.ctrl = reinterpret_cast<uint32_t*>(wsb);
     a.wfmt = c.wfmt;
     return SPICE_OK;

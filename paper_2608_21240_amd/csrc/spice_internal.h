@@ -46,6 +46,8 @@ struct WsLayout {
     size_t hs;      // shared-block intermediate [T][I_s + kHPad] (dtype)
     size_t u;       // LoRE A x, fp32 [T*K][r]
     size_t sgate;   // output gate of the shared block, fp32 [T]
+    size_t base;    // bytes every call needs
+    size_t part;    // the shared block's partial results, fp32 [parts][T][d] (used when the workspace has them)
     size_t total;
 };
 WsLayout ws_layout(const spice_moe_cfg_t& c, int32_t T);
@@ -114,6 +116,7 @@ struct FfnArgs {
     void* h;        // workspace [T*K][I]
     void* hs;       // workspace [T][I_s]
     float* u;       // workspace [T*K][r]
+    float* part;    // workspace [parts][T][d], or null: the shared block's down pass is not split
     uint32_t* ctrl;
 };
 
@@ -159,24 +162,64 @@ struct CombineArgs {
     void* out;
 };
 
-// Grouped MFMA GEMMs of the HIT experts and the shared block for large token
-// counts (bf16; used by launch_expert_ffn when expert_gemm_applies).
-constexpr int kGemmMinTokens = 256;
+// Grouped MFMA GEMMs of the HIT experts, the shared block and the LoRE correction for many
+// tokens (bf16; used by launch_expert_ffn when expert_gemm_applies).
+// Fewest tokens of a call that takes them.  Below, the streaming tiles: one pass over the
+// shared block's weights per 32 tokens, but the routing runs beside the shared block.  Streaming
+// tiles / GEMMs, us per call: DeepSeek-V2-Lite sizes, 48 experts resident, T = 40 177 / 184,
+// T = 64 204 / 187 (8 resident: 88 / 82); Qwen2 sizes, whose shared block is 440 MB, T = 24
+// 310 / 315, T = 32 577 / 549, T = 48 677 / 561.
+constexpr int kGemmMinTokens = 64, kGemmMinTokensWide = 32;
+inline int gemm_min_tokens(int32_t d, int32_t Is) {
+    return (int64_t)3 * Is * d * 2 >= (64 << 20) ? kGemmMinTokensWide : kGemmMinTokens;
+}
+// Tile shape by the mean bucket size: a tile as tall as the buckets are long reads each weight
+// once and wastes no token column, and the more weight rows a block takes the more bytes it
+// keeps in flight.  Small / Wide / Big, us per call: n = 18 212 / 216 / 258, n = 48 223 / 211 /
+// 259, n = 94 293 / 266 / 280 (DeepSeek-V2-Lite sizes), n = 128 1774 / 1403 / 1359 (Qwen2).
+enum : int { kGemmSmall = 0, kGemmWide = 1, kGemmBig = 2 };
+// weight rows, tokens
+constexpr int kGemmSmallTile[2] = {128, 64}, kGemmWideTile[2] = {256, 128}, kGemmBigTile[2] = {256, 256};
+inline int gemm_shape(int32_t T, int32_t N, int32_t K) {
+    const int64_t n = (int64_t)T * K / (N > 0 ? N : 1);
+    return n < 32 ? kGemmSmall : n < 120 ? kGemmWide : kGemmBig;
+}
+// Splits of the shared block's down contraction.  Its tiles are Is / I times as long as a
+// routed expert's; with few of them (small T) the launch would wait for them at its end (Qwen2,
+// T = 96: 738 us whole, 604 in 8 parts).  At most as many as the GPU takes at a time (one Big
+// block per CU, two of the others): more only add partial sums (T = 2048: 2117 -> 2166).
+constexpr int kMaxSharedParts = 8;
+inline int gemm_shared_parts(int32_t T, int32_t d, int32_t N, int32_t K, int32_t C, int32_t I, int32_t Is) {
+    const int shape = gemm_shape(T, N, K);
+    if (T < gemm_min_tokens(d, Is) || Is <= 0) return 1;
+    const int* t = shape == kGemmBig ? kGemmBigTile : shape == kGemmWide ? kGemmWideTile : kGemmSmallTile;
+    const int64_t tiles = (int64_t)((T + t[1] - 1) / t[1]) * ((d + t[0] - 1) / t[0]);
+    const int64_t most = shape == kGemmBig ? 256 : 512;
+    int64_t p = C > 0 ? Is / I : kMaxSharedParts;  // no routed tiles: as many as fill the GPU
+    p = p < most / tiles ? p : most / tiles;
+    p = p < Is / 256 ? p : Is / 256;
+    return (int)(p < 1 ? 1 : p > kMaxSharedParts ? kMaxSharedParts : p);
+}
 
 struct GemmArgs {
-    int32_t T, d, N, K, C, I, Is;
-    int32_t ldh, ldhs;
+    int32_t T, d, N, K, C, I, Is, r;
+    int32_t do_hit;                    // HIT buckets too (else the shared block and LoRE only)
+    int32_t parts;                     // contraction splits of the shared block's down pass
     int32_t super_up[2], super_dn[2];  // shared-block super-tile (weight tiles, token tiles)
     const uint16_t* x;
     const int32_t* perm;
-    const int32_t* offsets;  // HIT class row of the bucket offsets
+    const int32_t* offsets;
     const int32_t* resident_slot;
     const uint16_t* w13_pool;
     const uint16_t* w2_pool;
     const uint16_t* w13s;
     const uint16_t* w2s;
+    const uint16_t* lore_A;
+    const uint16_t* lore_B;
     uint16_t* h;
     uint16_t* hs;
+    float* u;
+    float* part;                       // [parts][T][d] when parts > 1
     float* y_slots;
     float* y_shared;
     const float* sgate;  // nullable, as in FfnArgs

@@ -1,0 +1,49 @@
+"""GPU parity of the grouped GEMM tiles where they can go wrong: contractions, rows, ranks and
+buckets that are no multiple of a tile, each of the tile shapes, the split of the shared
+block's down pass (and a workspace without room for it), gated and absent shared blocks, and
+the separate LoRE call.  Every token against the oracle."""
+import pytest
+import torch
+
+from paper_2608_21240_amd import layer as LY, workloads as W
+from parity import Case, say
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(d, N, K, I, Is, r):
+    return W.MoEShape(d=d, n_experts=N, top_k=K, inter=I, shared_inter=Is, lore_rank=r, dtype=W.DTYPE_BF16)
+
+
+SMALL = shape(200, 20, 5, 104, 168, 24)     # buckets of 16-32: 128 x 64 tiles, k tails of 8 and 40
+WIDE = shape(264, 6, 3, 72, 2064, 136)      # buckets of 32-120, 256 x 128 tiles; shared block split in 8
+BIG = shape(520, 4, 2, 136, 264, 40)        # buckets of 150: 256 x 256 tiles
+NO_SHARED = shape(256, 8, 2, 128, 0, 16)
+
+
+@pytest.mark.parametrize("layer_call", [True, False])
+@pytest.mark.parametrize("s,T,R,gate,fused", [
+    (SMALL, 63, 9, False, True), (SMALL, 64, 9, False, True), (SMALL, 65, 20, True, True),
+    (SMALL, 130, 3, False, False), (WIDE, 96, 3, True, True), (WIDE, 209, 2, False, True), (BIG, 300, 2, False, True),
+    (BIG, 257, 4, True, True), (NO_SHARED, 129, 4, False, True), (NO_SHARED, 64, 1, False, False)])
+def test_gemm_edges(s, T, R, gate, fused, layer_call):
+    say(f"gemm d={s.d} I={s.inter} Is={s.shared_inter} T={T} R={R} gate={gate} fused={fused}")
+    c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=True, shared_gate=gate))
+    c.run_gpu(fused=fused, layer_call=layer_call)
+    c.run_oracle()
+    c.check_routing()
+    c.check_outputs()
+
+
+def test_workspace_without_room_for_the_split():
+    """A workspace of the size every call needs, but not of the split's partial results."""
+    say("gemm without the split's workspace")
+    c = Case(W.Workload("gemm", WIDE, tokens=96, resident=3, skew=True))
+    dev = LY.DeviceLayer(c.host)
+    run = LY.LayerRun(WIDE, 96, dev.C, keep_logits=True)
+    run.ws_bytes -= 256
+    run.ws = torch.zeros(run.ws_bytes, dtype=torch.uint8, device="cuda")
+    c.run_gpu(dev=dev, run=run)
+    c.run_oracle()
+    c.check_routing()
+    c.check_outputs()
