@@ -102,8 +102,9 @@ typedef struct {
  *   such blob.  Needs dtype SPICE_BF16 (activations, router, shared block and LoRE factors
  *   stay bf16), d and inter multiples of 32 and at most SPICE_MXFP4_MAX_K, and blobs below
  *   2 GiB.  The fetched-expert split (moe_split_plan,
- *   moe_fetch_experts, moe_expert_ffn_fetched) and moe_lore_fit return UNSUPPORTED for it;
- *   at any T the expert FFN runs on the streaming kernels, not the prefill GEMMs. */
+ *   moe_fetch_experts, moe_expert_ffn_fetched) and moe_lore_fit return UNSUPPORTED for it.
+ *   With many tokens the expert FFN runs on the prefill GEMMs where d and inter are
+ *   multiples of 128 and the pools 16-byte aligned, otherwise on the streaming kernels. */
 enum { SPICE_WFMT_DTYPE = 0, SPICE_WFMT_MXFP4 = 2 };
 #define SPICE_MXFP4_MAX_K 4096
 
@@ -257,7 +258,7 @@ spice_status_t moe_combine(const spice_moe_cfg_t* cfg, int32_t T, const float* t
  * combine with `resid` (as moe_combine).  Every output is the one those calls define.
  * The work that does not depend on routing is not ordered after it (Sec. 4.2: the shared
  * block S is always resident): for T <= 256 and T*K <= 1024 (routed experts in the cfg
- * dtype or in MXFP4; bf16 dtype experts only while the prefill GEMMs do not apply) the call is
+ * dtype or in MXFP4; bf16 activations only while the prefill GEMMs do not apply) the call is
  * three launches in which routing runs beside the shared block's up projection, the
  * shared block's down projection beside the routed up projections, and each routed tile
  * finds its bucket from the routing itself; otherwise the separate launches of those calls.

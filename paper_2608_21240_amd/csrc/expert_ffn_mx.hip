@@ -76,6 +76,7 @@ hipError_t launch_expert_ffn_mx(const FfnArgs& a, hipStream_t s) {
     const bool hit = (a.groups & kDoHit) != 0;
     const bool shared = (a.groups & kDoShared) != 0 && a.Is > 0;
     const bool lore = (a.groups & kDoLore) != 0 && a.r > 0;
+    if (expert_gemm_applies(a)) return launch_expert_gemm(a, hit, shared, s);
     Grid up, dn;
     ffn_grids(a, hit, shared, lore, up, dn);
     if (hit) {  // the MXFP4 HIT tiles are taller

@@ -169,9 +169,11 @@ struct CombineArgs {
 // tiles / GEMMs, us per call: DeepSeek-V2-Lite sizes, 48 experts resident, T = 40 177 / 184,
 // T = 64 204 / 187 (8 resident: 88 / 82); Qwen2 sizes, whose shared block is 440 MB, T = 24
 // 310 / 315, T = 32 577 / 549, T = 48 677 / 561.
+// MXFP4 experts: T = 64 115 / 118, T = 96 140 / 125; Qwen2 sizes T = 32 351 / 375, T = 64 483 / 393.
 constexpr int kGemmMinTokens = 64, kGemmMinTokensWide = 32;
-inline int gemm_min_tokens(int32_t d, int32_t Is) {
-    return (int64_t)3 * Is * d * 2 >= (64 << 20) ? kGemmMinTokensWide : kGemmMinTokens;
+inline int gemm_min_tokens(int32_t d, int32_t Is, int32_t wfmt) {
+    const int n = (int64_t)3 * Is * d * 2 >= (64 << 20) ? kGemmMinTokensWide : kGemmMinTokens;
+    return wfmt == SPICE_WFMT_MXFP4 ? n + 8 : n;
 }
 // Tile shape by the mean bucket size: a tile as tall as the buckets are long reads each weight
 // once and wastes no token column, and the more weight rows a block takes the more bytes it
@@ -191,7 +193,7 @@ inline int gemm_shape(int32_t T, int32_t N, int32_t K) {
 constexpr int kMaxSharedParts = 8;
 inline int gemm_shared_parts(int32_t T, int32_t d, int32_t N, int32_t K, int32_t C, int32_t I, int32_t Is) {
     const int shape = gemm_shape(T, N, K);
-    if (T < gemm_min_tokens(d, Is) || Is <= 0) return 1;
+    if (T < gemm_min_tokens(d, Is, SPICE_WFMT_DTYPE) || Is <= 0) return 1;
     const int* t = shape == kGemmBig ? kGemmBigTile : shape == kGemmWide ? kGemmWideTile : kGemmSmallTile;
     const int64_t tiles = (int64_t)((T + t[1] - 1) / t[1]) * ((d + t[0] - 1) / t[0]);
     const int64_t most = shape == kGemmBig ? 256 : 512;
@@ -210,8 +212,8 @@ struct GemmArgs {
     const int32_t* perm;
     const int32_t* offsets;
     const int32_t* resident_slot;
-    const uint16_t* w13_pool;
-    const uint16_t* w2_pool;
+    const void* w13_pool;
+    const void* w2_pool;
     const uint16_t* w13s;
     const uint16_t* w2s;
     const uint16_t* lore_A;

@@ -35,6 +35,21 @@ def test_gemm_edges(s, T, R, gate, fused, layer_call):
     c.check_outputs()
 
 
+MX_SMALL = shape(256, 12, 3, 128, 168, 24)  # MXFP4: 2 stages up, 1 down; buckets of 24
+MX_WIDE = shape(384, 6, 3, 256, 1096, 40)   # buckets of 96 and more: 256 x 128 tiles
+
+
+@pytest.mark.parametrize("s,T,R", [(MX_SMALL, 71, 12), (MX_SMALL, 72, 5), (MX_SMALL, 97, 12), (MX_WIDE, 200, 3),
+                                   (MX_WIDE, 333, 6)])
+def test_gemm_mxfp4_edges(s, T, R):
+    say(f"gemm mxfp4 d={s.d} I={s.inter} T={T} R={R}")
+    c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=True, wfmt=W.WFMT_MXFP4))
+    c.run_gpu()
+    c.run_oracle()
+    c.check_routing()
+    c.check_outputs()
+
+
 def test_workspace_without_room_for_the_split():
     """A workspace of the size every call needs, but not of the split's partial results."""
     say("gemm without the split's workspace")
