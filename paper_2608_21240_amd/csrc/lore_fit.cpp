@@ -6,11 +6,14 @@
 // map is the truncated SVD of Y carried back through X's pseudo-inverse:
 //   Y = U S V^T,  B = U_r = Y V_r S_r^-1,  A = S_r V_r^T (X^T X)^-1 X^T,
 //   loss = sum_{i > r} s_i^2.
-// Everything n-dimensional is done on the host in fp64 from the two n x n Gram matrices
-// X^T X and Y^T Y (computed on the GPU in fp64): Y^T Y = V S^2 V^T by Jacobi rotations
-// (round-robin order), (X^T X) Z = V_r S_r by Cholesky.  The GPU computes E_e(x) and S(x) with the
-// grouped-FFN kernels (a one-expert bucket of all n tokens), the residual, the Gram
-// matrices and the final d x r products.
+// Everything n-dimensional is done in fp64 from the two n x n Gram matrices X^T X and Y^T Y
+// (computed on the GPU in fp64): Y^T Y = V S^2 V^T, (X^T X) Z = V_r S_r by Cholesky.  Up to
+// kFitHostTokens tokens both run on the host, the first by Jacobi rotations (round-robin
+// order).  With more, the GPU reduces Y^T Y to tridiagonal form by Householder steps, the host
+// runs the implicit QR iteration on its two diagonals, and the GPU applies the iteration's
+// rotations to the eigenvectors meanwhile, carries the leading ones back, factors X^T X and
+// solves.  The GPU also computes E_e(x) and S(x) with the grouped-FFN kernels (a one-expert
+// bucket of all n tokens), the residual, the Gram matrices and the final d x r products.
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -31,6 +34,13 @@ spice_status_t validate(const spice_moe_cfg_t* cfg, int32_t T);
 namespace {
 
 constexpr int32_t kMaxFitTokens = 1024;
+// Most tokens whose eigenproblem and solve stay on the host: below, they take less time there
+// than the GPU path's launches, one per Householder step (GPU / host, ms per fit: n = 49
+// 1.04 / 1.14, n = 64 1.22 / 2.17, n = 128 2.3 / 14.3, n = 256 5.0 / 118).
+constexpr int32_t kFitHostTokens = 48;
+// Rotations (and sweeps) handed to the GPU at a time, and the device's ring of such batches.
+constexpr size_t kRotBatch = 32768;
+constexpr int kRotRing = 4;
 
 spice_status_t err(spice_status_t st, const std::string& m) { return spice::set_error(st, m.c_str()); }
 
@@ -47,7 +57,10 @@ spice_moe_cfg_t one_expert(const spice_moe_cfg_t& c) {
 }
 
 struct FitLayout {
-    size_t ffn_ws, perm, offsets, resident, y, ys, gx, gy, coef_a, coef_b, total;
+    size_t ffn_ws, perm, offsets, resident, y, ys, gx, gy, coef_a, coef_b;
+    size_t base;  // bytes every call needs
+    // the GPU eigensolver's and solve's (used when the workspace has them)
+    size_t refl, zt, chol, vec, small, rot, sweeps, total;
 };
 
 FitLayout fit_layout(const spice_moe_cfg_t& c, int32_t n, int32_t r) {
@@ -64,6 +77,17 @@ FitLayout fit_layout(const spice_moe_cfg_t& c, int32_t n, int32_t r) {
     L.gy = off;       off += align256((size_t)n * n * 8);
     L.coef_a = off;   off += align256((size_t)n * r * 8);
     L.coef_b = off;   off += align256((size_t)n * r * 8);
+    L.base = off;
+    if (n > kFitHostTokens) {
+        L.refl = off;   off += align256((size_t)n * n * 8);
+        L.zt = off;     off += align256((size_t)n * n * 8);
+        L.chol = off;   off += align256((size_t)n * n * 8);
+        L.vec = off;    off += align256((size_t)std::min(n, r) * n * 8);
+        // tau, p (two), diagonal, subdiagonal, singular values [r], order [n], flag
+        L.small = off;  off += align256((size_t)n * 5 * 8 + (size_t)r * 8 + (size_t)n * 4 + 4);
+        L.rot = off;    off += kRotRing * kRotBatch * 16;
+        L.sweeps = off; off += kRotRing * kRotBatch * 8;
+    }
     L.total = off;
     return L;
 }
@@ -139,6 +163,67 @@ void jacobi_eigen(int n, std::vector<double>& a, std::vector<double>& w, std::ve
     for (int i = 0; i < n; ++i) w[i] = a[(size_t)i * n + i];
 }
 
+// Implicit QR iteration with Wilkinson shifts on the symmetric tridiagonal matrix with diagonal
+// d[n] and subdiagonal e[n - 1] (both overwritten; d ends as the eigenvalues, unordered).  Every
+// QR step chases its bulge from row lo to row hi by the plane rotations (k, k + 1), k = lo ..
+// hi - 1, which it hands to sweep(lo, hi - lo, c and s of each): a vector of the eigenvector
+// matrix (started as the identity) turns as z_k' = c z_k + s z_k+1, z_k+1' = c z_k+1 - s z_k.
+// False if it does not converge (entries that are not finite).
+template <class Sweep>
+bool tridiag_qr(int n, std::vector<double>& d, std::vector<double>& e, Sweep sweep) {
+    double scale = 0.0;
+    for (int i = 0; i < n; ++i) {
+        if (!std::isfinite(d[i]) || (i + 1 < n && !std::isfinite(e[i]))) return false;
+        scale = std::max({scale, std::fabs(d[i]), i + 1 < n ? std::fabs(e[i]) : 0.0});
+    }
+    if (scale == 0.0) return true;
+    for (int i = 0; i < n; ++i) {
+        d[i] /= scale;
+        if (i + 1 < n) e[i] /= scale;
+    }
+    // an off-diagonal below the rounding of its neighbours (or of a hundredth of the largest
+    // entry, far below the rounding of the matrix) is zero
+    const double eps = 2.220446049250313e-16;
+    auto small = [&](int k) { return std::fabs(e[k]) <= eps * std::max(std::fabs(d[k]) + std::fabs(d[k + 1]), 1e-2); };
+    std::vector<double> cs;
+    long left = 60L * n;
+    for (int hi = n - 1; hi > 0;) {
+        if (small(hi - 1)) {
+            e[--hi] = 0.0;
+            continue;
+        }
+        int lo = hi - 1;
+        while (lo > 0 && !small(lo - 1)) --lo;
+        if (--left < 0) return false;
+        // the eigenvalue of the trailing 2 x 2 block nearer to its last entry
+        const double a = 0.5 * (d[hi - 1] - d[hi]), b = e[hi - 1];
+        const double shift = d[hi] - b * b / (a + std::copysign(std::sqrt(a * a + b * b), a));
+        double x = d[lo] - shift, z = e[lo];
+        cs.clear();
+        for (int k = lo; k < hi; ++k) {
+            const double r = std::sqrt(x * x + z * z);
+            const double inv = r > 0.0 ? 1.0 / r : 0.0;
+            const double c = r > 0.0 ? x * inv : 1.0, s = z * inv;
+            if (k > lo) e[k - 1] = r;
+            const double d0 = d[k], d1 = d[k + 1], ek = e[k];
+            const double t = s * (d1 - d0) + 2.0 * c * ek;
+            d[k] = d0 + s * t;
+            d[k + 1] = d1 - s * t;
+            e[k] = c * t - ek;
+            if (k + 1 < hi) {
+                x = e[k];
+                z = s * e[k + 1];
+                e[k + 1] *= c;
+            }
+            cs.push_back(c);
+            cs.push_back(s);
+        }
+        sweep(lo, hi - lo, cs);
+    }
+    for (int i = 0; i < n; ++i) d[i] *= scale;
+    return true;
+}
+
 // Cholesky factor of the SPD n x n matrix g (row-major, lower factor in place); false if
 // it is not positive definite.
 bool cholesky(int n, std::vector<double>& g) {
@@ -171,6 +256,101 @@ void cholesky_solve(int n, const std::vector<double>& l, double* b) {
     }
 }
 
+const char kDependent[] = "moe_lore_fit: the calibration tokens are linearly dependent";
+
+// Indices of the eigenvalues, largest first.
+std::vector<int32_t> by_size(const std::vector<double>& ev) {
+    std::vector<int32_t> ord(ev.size());
+    for (size_t i = 0; i < ord.size(); ++i) ord[i] = (int32_t)i;
+    std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b) { return ev[a] > ev[b]; });
+    return ord;
+}
+
+// Eq. 10's minimum: the squared singular values beyond the r-th.
+double tail_loss(const std::vector<double>& ev, const std::vector<int32_t>& ord, int32_t r) {
+    double loss = 0.0;
+    for (size_t i = (size_t)r; i < ord.size(); ++i) loss += std::max(ev[ord[i]], 0.0);
+    return loss;
+}
+
+// The r leading singular values, 0 for directions beyond n or with none (they give zero rows
+// of A and columns of B).
+std::vector<double> singular_values(const std::vector<double>& ev, const std::vector<int32_t>& ord, int32_t r) {
+    std::vector<double> sv((size_t)r, 0.0);
+    const double s_max = std::sqrt(std::max(ev[ord[0]], 0.0));
+    for (int32_t j = 0; j < std::min<int32_t>(r, (int32_t)ord.size()); ++j) {
+        const double sj = std::sqrt(std::max(ev[ord[j]], 0.0));
+        if (sj > 1e-12 * s_max) sv[j] = sj;
+    }
+    return sv;
+}
+
+// The coefficients da, db and the loss with the n x n work on the GPU (gx is only read up to its
+// factor's copy, gy is destroyed).  done = 0 if the iteration does not converge.
+spice_status_t gpu_coefficients(char* w, const FitLayout& L, int32_t n, int32_t r, double* gx, double* gy, double* da,
+                                double* db, uint32_t& flags, double* loss_out, hipError_t e, hipStream_t s, int& done) {
+    auto at = [&](size_t off) { return reinterpret_cast<double*>(w + off); };
+    double *refl = at(L.refl), *zt = at(L.zt), *chol = at(L.chol), *vec = at(L.vec);
+    double *tau = at(L.small), *p = tau + n, *dv = p + 2 * n, *ev_ = dv + n, *svd = ev_ + n;
+    int32_t* ordd = reinterpret_cast<int32_t*>(svd + r);
+    uint32_t* bad = reinterpret_cast<uint32_t*>(ordd + n);
+    auto hip = [](hipError_t x) { return err(SPICE_ERR_HIP, std::string("moe_lore_fit: ") + hipGetErrorString(x)); };
+    if (e == hipSuccess) e = spice::launch_fit_tridiag(n, gy, refl, tau, p, dv, ev_, s);
+    std::vector<double> d(n), sub(n);
+    if (e == hipSuccess) e = hipMemcpyAsync(d.data(), dv, (size_t)n * 8, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(sub.data(), ev_, (size_t)(n - 1) * 8, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip(e);
+    if (flags) return err(SPICE_ERR_INTERNAL, "moe_lore_fit: FFN device flags raised");
+    // the factor of X^T X runs while the host iterates, and the iteration's rotations follow it in
+    // batches, each copied into its place in the ring
+    e = spice::launch_fill_u32(bad, 1, 0u, s);
+    if (e == hipSuccess) e = spice::launch_fit_chol(n, gx, chol, bad, s);
+    std::vector<double> rot[kRotRing];
+    std::vector<int32_t> sw[kRotRing];
+    int slot = 0;
+    bool first = true;
+    auto flush = [&]() {
+        if (e == hipSuccess) e = hipMemcpyAsync(at(L.rot) + slot * kRotBatch * 2, rot[slot].data(), rot[slot].size() * 8, hipMemcpyHostToDevice, s);
+        int32_t* dsw = reinterpret_cast<int32_t*>(w + L.sweeps) + slot * kRotBatch * 2;
+        if (e == hipSuccess) e = hipMemcpyAsync(dsw, sw[slot].data(), sw[slot].size() * 4, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = spice::launch_fit_rotate(n, at(L.rot) + slot * kRotBatch * 2, dsw, (int32_t)(sw[slot].size() / 2), first, zt, s);
+        first = false;
+        if (++slot == kRotRing) {  // the ring's host copies are reused
+            slot = 0;
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+        }
+        rot[slot].clear();
+        sw[slot].clear();
+    };
+    const bool ok = tridiag_qr(n, d, sub, [&](int lo, int cnt, const std::vector<double>& cs) {
+        if (rot[slot].size() + cs.size() > 2 * kRotBatch) flush();
+        rot[slot].insert(rot[slot].end(), cs.begin(), cs.end());
+        sw[slot].push_back(lo);
+        sw[slot].push_back(cnt);
+    });
+    if (ok) flush();  // with no rotation at all it still writes the identity
+    const std::vector<int32_t> ord = by_size(d);
+    const std::vector<double> sv = singular_values(d, ord, r);
+    uint32_t dependent = 0;
+    if (ok && e == hipSuccess) {
+        e = hipMemcpyAsync(ordd, ord.data(), (size_t)n * 4, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(svd, sv.data(), (size_t)r * 8, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = spice::launch_fit_back(n, std::min(n, r), zt, ordd, refl, tau, vec, s);
+        if (e == hipSuccess) e = spice::launch_fit_solve(n, r, chol, vec, svd, da, db, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&dependent, bad, 4, hipMemcpyDeviceToHost, s);
+    }
+    const hipError_t drained = hipStreamSynchronize(s);  // the host buffers above are read by the copies
+    if (e == hipSuccess) e = drained;
+    if (e != hipSuccess) return hip(e);
+    if (!ok) return SPICE_OK;
+    if (loss_out) *loss_out = tail_loss(d, ord, r);
+    if (dependent) return err(SPICE_ERR_INVALID, kDependent);
+    done = 1;
+    return SPICE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -199,9 +379,9 @@ spice_status_t moe_lore_fit(const spice_moe_cfg_t* cfg, int32_t n, int32_t r, co
         if (c.shared_inter > 0 && (!w13_shared || !w2_shared))
             return err(SPICE_ERR_INVALID, "moe_lore_fit: shared-block weights are NULL");
         const FitLayout L = fit_layout(c, n, r);
-        if (ws_bytes < L.total)
+        if (ws_bytes < L.base)
             return err(SPICE_ERR_WORKSPACE, "moe_lore_fit: workspace has " + std::to_string(ws_bytes) +
-                                                " bytes, needs " + std::to_string(L.total));
+                                                " bytes, needs " + std::to_string(L.base));
         char* w = static_cast<char*>(ws);
         hipStream_t s = stream;
         const spice_moe_cfg_t o = one_expert(c);
@@ -237,42 +417,49 @@ spice_status_t moe_lore_fit(const spice_moe_cfg_t* cfg, int32_t n, int32_t r, co
         if (e == hipSuccess && c.shared_inter > 0) e = spice::launch_fit_residual((size_t)n * d, y, ys, s);
         if (e == hipSuccess) e = spice::launch_fit_gram(n, d, c.dtype, x, gx, s);
         if (e == hipSuccess) e = spice::launch_fit_gram(n, d, SPICE_F32, y, gy, s);
-        std::vector<double> hx((size_t)n * n), hy((size_t)n * n);
-        uint32_t flags = 0;
-        if (e == hipSuccess) e = hipMemcpyAsync(hx.data(), gx, hx.size() * 8, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(hy.data(), gy, hy.size() * 8, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(&flags, fw, 4, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return err(SPICE_ERR_HIP, std::string("moe_lore_fit: ") + hipGetErrorString(e));
-        if (flags) return err(SPICE_ERR_INTERNAL, "moe_lore_fit: FFN device flags raised");
-
-        // Y^T Y = V S^2 V^T; order by eigenvalue, largest first
-        std::vector<double> ev, vec;
-        jacobi_eigen(n, hy, ev, vec);
-        std::vector<int> ord(n);
-        for (int i = 0; i < n; ++i) ord[i] = i;
-        std::stable_sort(ord.begin(), ord.end(), [&](int a_, int b_) { return ev[a_] > ev[b_]; });
-        double loss = 0.0;
-        for (int i = r; i < n; ++i) loss += std::max(ev[ord[i]], 0.0);
-        if (loss_out) *loss_out = loss;
-        if (!cholesky(n, hx))
-            return err(SPICE_ERR_INVALID, "moe_lore_fit: the calibration tokens are linearly dependent");
-        // coef_a = (X^T X)^-1 V_r S_r (n x r), coef_b = V_r S_r^-1 (n x r); directions beyond
-        // n or with s = 0 give zero rows of A and columns of B
-        const double s_max = std::sqrt(std::max(ev[ord[0]], 0.0));
-        std::vector<double> ca((size_t)n * r, 0.0), cb((size_t)n * r, 0.0), col(n);
-        for (int j = 0; j < std::min(r, n); ++j) {
-            const double sj = std::sqrt(std::max(ev[ord[j]], 0.0));
-            if (!(sj > 1e-12 * s_max)) continue;
-            for (int i = 0; i < n; ++i) col[i] = vec[(size_t)n * ord[j] + i] * sj;
-            for (int i = 0; i < n; ++i) cb[(size_t)i * r + j] = vec[(size_t)n * ord[j] + i] / sj;
-            cholesky_solve(n, hx, col.data());
-            for (int i = 0; i < n; ++i) ca[(size_t)i * r + j] = col[i];
-        }
         double* da = reinterpret_cast<double*>(w + L.coef_a);
         double* db = reinterpret_cast<double*>(w + L.coef_b);
-        e = hipMemcpyAsync(da, ca.data(), ca.size() * 8, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(db, cb.data(), cb.size() * 8, hipMemcpyHostToDevice, s);
+        uint32_t flags = 0;
+        if (e == hipSuccess) e = hipMemcpyAsync(&flags, fw, 4, hipMemcpyDeviceToHost, s);
+        std::vector<double> ca, cb;  // alive until the copies of them are done
+        int done = 0;
+        if (n > kFitHostTokens && ws_bytes >= L.total) {
+            // on failure to converge (a matrix that is not finite) the host path below decides
+            const spice_status_t g = gpu_coefficients(w, L, n, r, gx, gy, da, db, flags, loss_out, e, s, done);
+            if (g != SPICE_OK) return g;
+            if (!done) e = spice::launch_fit_gram(n, d, SPICE_F32, y, gy, s);  // reduced in place above
+            if (!done && e == hipSuccess) e = spice::launch_fit_gram(n, d, c.dtype, x, gx, s);
+        }
+        if (!done) {
+            std::vector<double> hx((size_t)n * n), hy((size_t)n * n);
+            if (e == hipSuccess) e = hipMemcpyAsync(hx.data(), gx, hx.size() * 8, hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipMemcpyAsync(hy.data(), gy, hy.size() * 8, hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) return err(SPICE_ERR_HIP, std::string("moe_lore_fit: ") + hipGetErrorString(e));
+            if (flags) return err(SPICE_ERR_INTERNAL, "moe_lore_fit: FFN device flags raised");
+
+            // Y^T Y = V S^2 V^T; order by eigenvalue, largest first
+            std::vector<double> ev, vec;
+            jacobi_eigen(n, hy, ev, vec);
+            const std::vector<int32_t> ord = by_size(ev);
+            if (loss_out) *loss_out = tail_loss(ev, ord, r);
+            if (!cholesky(n, hx)) return err(SPICE_ERR_INVALID, kDependent);
+            // coef_a = (X^T X)^-1 V_r S_r (n x r), coef_b = V_r S_r^-1 (n x r)
+            const std::vector<double> sv = singular_values(ev, ord, r);
+            std::vector<double> col(n);
+            ca.assign((size_t)n * r, 0.0);
+            cb.assign((size_t)n * r, 0.0);
+            for (int j = 0; j < std::min(r, n); ++j) {
+                const double sj = sv[j];
+                if (!(sj > 0.0)) continue;
+                for (int i = 0; i < n; ++i) col[i] = vec[(size_t)n * ord[j] + i] * sj;
+                for (int i = 0; i < n; ++i) cb[(size_t)i * r + j] = vec[(size_t)n * ord[j] + i] / sj;
+                cholesky_solve(n, hx, col.data());
+                for (int i = 0; i < n; ++i) ca[(size_t)i * r + j] = col[i];
+            }
+            e = hipMemcpyAsync(da, ca.data(), ca.size() * 8, hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipMemcpyAsync(db, cb.data(), cb.size() * 8, hipMemcpyHostToDevice, s);
+        }
         if (e == hipSuccess) e = spice::launch_fit_project(n, d, r, c.dtype, x, da, A_out, false, s);
         if (e == hipSuccess) e = spice::launch_fit_project(n, d, r, SPICE_F32, y, db, B_out, true, s);
         if (e == hipSuccess && y_out) e = hipMemcpyAsync(y_out, y, (size_t)n * d * 4, hipMemcpyDeviceToDevice, s);

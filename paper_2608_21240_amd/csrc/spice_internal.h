@@ -251,6 +251,15 @@ hipError_t launch_fit_residual(size_t count, float* y, const float* shared, hipS
 hipError_t launch_fit_gram(int32_t n, int32_t d, int dtype, const void* M, double* G, hipStream_t s);
 hipError_t launch_fit_project(int32_t n, int32_t d, int32_t r, int dtype, const void* M, const double* C, float* out,
                               bool b_layout, hipStream_t s);
+// Eigen-decomposition and SPD solve of the fit, n <= 1024 (device pointers; see the kernels).
+hipError_t launch_fit_tridiag(int32_t n, double* A, double* V, double* tau, double* p, double* dv, double* ev, hipStream_t s);
+hipError_t launch_fit_rotate(int32_t n, const double* rot, const int32_t* sweeps, int32_t nsweeps, bool first, double* Zt,
+                             hipStream_t s);
+hipError_t launch_fit_back(int32_t n, int32_t m, const double* Zt, const int32_t* ord, const double* V, const double* tau,
+                           double* vec, hipStream_t s);
+hipError_t launch_fit_chol(int32_t n, double* G, double* L, uint32_t* bad, hipStream_t s);
+hipError_t launch_fit_solve(int32_t n, int32_t r, const double* L, const double* vec, const double* sv, double* ca,
+                            double* cb, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, size_t words, uint32_t value, hipStream_t s);
 
 }  // namespace spice

@@ -22,5 +22,18 @@ hipError_t launch_fit_gram(int32_t, int32_t, int, const void*, double*, hipStrea
 hipError_t launch_fit_project(int32_t, int32_t, int32_t, int, const void*, const double*, float*, bool, hipStream_t) {
     return hipErrorNoDevice;
 }
+hipError_t launch_fit_tridiag(int32_t, double*, double*, double*, double*, double*, double*, hipStream_t) {
+    return hipErrorNoDevice;
+}
+hipError_t launch_fit_rotate(int32_t, const double*, const int32_t*, int32_t, bool, double*, hipStream_t) {
+    return hipErrorNoDevice;
+}
+hipError_t launch_fit_back(int32_t, int32_t, const double*, const int32_t*, const double*, const double*, double*, hipStream_t) {
+    return hipErrorNoDevice;
+}
+hipError_t launch_fit_chol(int32_t, double*, double*, uint32_t*, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_fit_solve(int32_t, int32_t, const double*, const double*, const double*, double*, double*, hipStream_t) {
+    return hipErrorNoDevice;
+}
 hipError_t launch_fill_u32(uint32_t*, size_t, uint32_t, hipStream_t) { return hipErrorNoDevice; }
 }  // namespace spice
