@@ -168,8 +168,8 @@ spice_status_t spice_wait_ready(const volatile uint32_t* ready, uint32_t value, 
  *   host_out      host copies for the CPU path (see spice_host_out_t), or NULL
  * The workspace also receives the device work lists of the buckets (per class, the
  * non-empty buckets in ascending expert order with start and size), which the fused
- * layer path reads.  T <= 256 runs one block per token and one bucketing block; larger
- * T computes the logits as fp64 MFMA tiles.
+ * layer path reads.  Up to 256 tokens the call is one launch; from 208 on the logits are
+ * computed as fp64 MFMA tiles.
  */
 spice_status_t moe_route_bucket(const spice_moe_cfg_t* cfg, int32_t T, const void* x,
                                 const void* w_gate, const float* logit_bias,

@@ -1,26 +1,35 @@
 // Router logits, softmax top-K gating, per-slot classification and (class, expert)
 // bucketing (Eq. 1; Sec. 2.1, 4.2, 4.3).  No block waits for another block.
 //
-// T <= kRouteTokenMaxT (decode), one launch (route_logits_kernel): a token's router rows
+// T < kRouteTiledMinT (decode), one launch (route_logits_kernel): a token's router rows
 //   are spread over several blocks (one row per wave), each summing its logits in fp64; the
 //   last of the token's blocks to finish (an arrival counter per token) takes the token's
 //   top-K, gates, confidence and classes and publishes them, with the slots' bucket keys,
 //   at the device-coherent level; the last of those blocks over all tokens (a second
 //   arrival counter) sorts the T*K slots by (class, expert), writes the work lists and,
 //   when asked, the CPU path's host copies and their ready word.
+// Up to kRouteTokenMaxT, one launch of route_tiled_kernel: per 16 tokens, the logits as fp64
+//   MFMA tiles of 16 experts x 16 tokens, the contraction split over several blocks whose
+//   last one adds their partial logits in order and takes the tokens' top-K, gates and
+//   classes; the last block over all tokens buckets the slots as above.
 // Larger T (prefill), three launches:
-//   1. route_prefill_kernel: per 16 tokens, the logits as fp64 MFMA tiles of 16 experts x
-//      16 tokens (two waves per tile, each half the contraction), then the tokens' top-K,
-//      gates and classes in the same block, and the block's histogram of bucket keys;
+//   1. route_tiled_kernel, whose last block per 16 tokens leaves a histogram of bucket keys;
 //   2. bucket_scan_kernel: a wave per bucket key turns its histogram row into each routing
-//      block's running count within the key and the key's total; the last scan block to
+//      group's running count within the key and the key's total; the last scan block to
 //      finish turns the totals into each key's start (offsets, work lists, class counts);
 //   3. bucket_scatter_kernel: per 16 tokens, the stable positions of their slots (perm,
 //      inv_perm).  The last scan block also writes the host copies when asked.
+// The tiled logits are bound by the fp64 matrix rate of the CUs that hold a block: with a block
+// per 16 tokens, 63 CUs at T = 1000; with the contraction split, all 256 (N = 64, d = 2048: the
+// three launches 40 -> 26 us).  Below kRouteTiledMinT the row-per-wave launch is shorter (rows /
+// tiles, us per call: T = 64 12.1 / 20.6, T = 192 20.3 / 21.6, T = 256 24.4 / 21.7; at d = 3584
+// T = 192 24.7 / 21.7).
 //
 // bf16 x bf16 and fp32 x fp32 products are exact in fp64, so on every path only the
 // summation order of the logits differs from a plain loop.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "route_device.h"
 
@@ -56,6 +65,7 @@ __global__ __launch_bounds__(kLogitThreads) void route_logits_kernel(RouteArgs a
 constexpr int kPrefillThreads = 1024;  // 16 waves
 constexpr int kGroupTiles = 2;          // expert tiles of 16 per routing wave
 constexpr int kPrefillTok = 16;       // tokens per prefill routing block (one MFMA tile wide)
+constexpr int kMaxParts = 8;          // contraction parts of a tiled routing group, a block each
 constexpr int kScanThreads = 1024;    // bucket_scan_kernel: a wave per key; the last block a thread per key
 constexpr int kScanKeys = kScanThreads / 64;  // bucket keys per scan block
 static_assert(3 * SPICE_MAX_EXPERTS <= kScanThreads, "a scan thread per bucket key");
@@ -147,16 +157,24 @@ __device__ __forceinline__ void prefill_group(const RouteArgs& a, const char* xr
     for (int i = 0; i < kGroupTiles; ++i) out[i] = acc[i][0] + acc[i][1];
 }
 
-// Prefill routing of tokens [16 b, 16 b + 16): logits, top-K, gates, classes, and the
-// block's histogram of bucket keys (column b of the table).
-template <int DT>
-__global__ __launch_bounds__(kPrefillThreads) void route_prefill_kernel(RouteArgs a) {
-    __shared__ PrefillLds L;
+constexpr int kTiledCache = 2048;  // slots whose keys stay in LDS while the last block buckets them
+constexpr size_t kTiledBucketLds = bucket_lds_bytes(kPrefillThreads, SPICE_MAX_EXPERTS, kTiledCache);
+
+// Tiled routing of the 16 tokens of group b / parts: the logits (part b % parts of the
+// contraction; the last of the group's blocks adds the parts in order), top-K, gates, classes.
+// kOne: the last block over all groups then buckets the slots (few tokens); otherwise the
+// group's histogram of bucket keys goes to column b / parts of the table.
+template <int DT, bool kOne>
+__global__ __launch_bounds__(kPrefillThreads) void route_tiled_kernel(RouteArgs a, int parts_k) {
+    __shared__ __align__(16) unsigned char s_raw[sizeof(PrefillLds) > kTiledBucketLds ? sizeof(PrefillLds) : kTiledBucketLds];
+    __shared__ int s_flag;
+    PrefillLds& L = *reinterpret_cast<PrefillLds*>(s_raw);
+    const int group = blockIdx.x / parts_k, part_k = blockIdx.x % parts_k;
     constexpr int kNW = kPrefillThreads / 64;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, q = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = a.N, K = a.K, NK = 3 * N;
-    const int t0 = blockIdx.x * kPrefillTok;
+    const int t0 = group * kPrefillTok;
     const int tok = t0 + m;
     const bool tok_ok = tok < a.T;
     const int es = RouteElem<DT>::es;
@@ -169,11 +187,12 @@ __global__ __launch_bounds__(kPrefillThreads) void route_prefill_kernel(RouteArg
     // then the parts are summed in order
     const int ntile = (N + 15) / 16, ngroups = (ntile + kGroupTiles - 1) / kGroupTiles, parts = kNW / ngroups;
     const int npass = (a.d + 8 * RouteElem<DT>::V - 1) / (8 * RouteElem<DT>::V);
+    const int pa = part_k * npass / parts_k, np = (part_k + 1) * npass / parts_k - pa;  // this block's passes
     if (w < ngroups * parts) {
         const int g = w / parts, kp = w - g * parts;
         const int ntg = min(kGroupTiles, ntile - kGroupTiles * g);
         f64x4_t part[kGroupTiles];
-        prefill_group<DT>(a, xr, kGroupTiles * g, ntg, kp * npass / parts, (kp + 1) * npass / parts, lane, part);
+        prefill_group<DT>(a, xr, kGroupTiles * g, ntg, pa + kp * np / parts, pa + (kp + 1) * np / parts, lane, part);
         // result layout of the f64 16x16x4 product: element v of lane (m, q) is expert
         // tile*16 + 4v + q for token t0 + m
 #pragma unroll
@@ -189,10 +208,36 @@ __global__ __launch_bounds__(kPrefillThreads) void route_prefill_kernel(RouteArg
         const int tt = i / N, ee = i - tt * N;
         double z = L.zp[tt * N + ee];
         for (int kp = 1; kp < parts; ++kp) z += L.zp[(kp * kPrefillTok + tt) * N + ee];
+        if (parts_k > 1) {  // written through to the device-coherent level (route_last_block)
+            __hip_atomic_store(reinterpret_cast<unsigned long long*>(a.part_ws) + (size_t)blockIdx.x * kPrefillTok * N + i,
+                               (unsigned long long)__double_as_longlong(z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            continue;
+        }
         z += a.bias ? (double)a.bias[ee] : 0.0;
         L.z[tt][ee] = z;
         L.key[tt][ee] = logit_key(z);
         if (a.logits_out && t0 + tt < a.T) a.logits_out[(size_t)(t0 + tt) * N + ee] = z;
+    }
+    if (parts_k > 1) {
+        if (!route_last_block(&a.ctrl[kWordTokCount + group * kTokCountStride], parts_k, &s_flag)) return;
+        const unsigned long long* zp =
+            reinterpret_cast<const unsigned long long*>(a.part_ws) + (size_t)group * parts_k * kPrefillTok * N;
+        for (int i = tid; i < kPrefillTok * N; i += kPrefillThreads) {
+            const int tt = i / N, ee = i - tt * N;
+            unsigned long long v[kMaxParts];
+#pragma unroll
+            for (int p = 0; p < kMaxParts; ++p)
+                if (p < parts_k)
+                    v[p] = __hip_atomic_load(zp + (size_t)p * kPrefillTok * N + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            double z = __longlong_as_double((long long)v[0]);
+#pragma unroll
+            for (int p = 1; p < kMaxParts; ++p)
+                if (p < parts_k) z += __longlong_as_double((long long)v[p]);
+            z += a.bias ? (double)a.bias[ee] : 0.0;
+            L.z[tt][ee] = z;
+            L.key[tt][ee] = logit_key(z);
+            if (a.logits_out && t0 + tt < a.T) a.logits_out[(size_t)(t0 + tt) * N + ee] = z;
+        }
     }
     __syncthreads();
 
@@ -226,15 +271,23 @@ __global__ __launch_bounds__(kPrefillThreads) void route_prefill_kernel(RouteArg
         const int tt = w + h * kNW, t = t0 + tt;
         if (t < a.T) {
             const float conf_in = (a.conf_mode == SPICE_CONF_INPUT && lane < K) ? a.conf[(size_t)t * K + lane] : 0.f;
-            const int key = wave_topk_gates(a, t, L.z[tt], L.res, L.pick[tt], lane, conf_in);
-            if (key >= 0) atomicAdd(&L.hist[key], 1);
+            const int key = wave_topk_gates<kOne>(a, t, L.z[tt], L.res, L.pick[tt], lane, conf_in);
+            if (!kOne && key >= 0) atomicAdd(&L.hist[key], 1);
         }
     }
+    if constexpr (kOne) {
+        // the published top-K outputs and keys of every token are at the device-coherent level
+        // once every group's last block has counted itself here
+        if (!route_last_block(&a.ctrl[kWordRouteDone], gridDim.x / parts_k, &s_flag)) return;
+        bucket_slots<kPrefillThreads, kTiledCache, true>(a, reinterpret_cast<int*>(s_raw));
+        if (a.hx || a.h_idx || a.h_w || a.h_cls || a.h_ready) mirror_host<kPrefillThreads, true>(a);
+        return;
+    }
     __syncthreads();
-    // as column blockIdx.x of the table
+    // as column `group` of the table
     int* table = reinterpret_cast<int*>(a.logits_ws);
     const int stride = prefill_hist_stride(a.T);
-    for (int k = tid; k < NK; k += kPrefillThreads) table[(size_t)k * stride + blockIdx.x] = L.hist[k];
+    for (int k = tid; k < NK; k += kPrefillThreads) table[(size_t)k * stride + group] = L.hist[k];
 }
 
 // Each wave: one key's exclusive running count over the routing blocks (in place) and its
@@ -385,24 +438,45 @@ __global__ __launch_bounds__(64) void bucket_scatter_kernel(RouteArgs a) {
 
 }  // namespace
 
+// Contraction parts per group of 16 tokens: as many as fill the 256 CUs with a block each (a
+// group's logits are bound by its CU's fp64 matrix rate), at least two 64- or 32-wide passes
+// per part, and partial logits that fit the workspace.
+static int routing_parts(const RouteArgs& a) {
+    const int groups = (a.T + kPrefillTok - 1) / kPrefillTok;
+    const int npass = a.d * (a.dtype == SPICE_BF16 ? 2 : 4) / 128;
+    const size_t per_part = (size_t)groups * kPrefillTok * a.N * sizeof(double);
+    int p = std::min({kMaxParts, 256 / groups, npass / 2});
+    if ((size_t)std::max(p, 0) * per_part > a.part_bytes) p = (int)(a.part_bytes / per_part);
+    return std::max(p, 1);
+}
+
 hipError_t launch_route_bucket(const RouteArgs& a, hipStream_t s) {
-    if (a.T <= kRouteTokenMaxT) {
+    const unsigned groups = (unsigned)((a.T + kPrefillTok - 1) / kPrefillTok);
+    if (a.T < kRouteTiledMinT) {
         const int g = route_blocks_per_token(a.N + (a.w_sg ? 1 : 0), kLogitThreads);
         const dim3 grid((unsigned)(a.T * g));
         if (a.dtype == SPICE_BF16)
             hipLaunchKernelGGL(route_logits_kernel<SPICE_BF16>, grid, dim3(kLogitThreads), 0, s, a, g);
         else
             hipLaunchKernelGGL(route_logits_kernel<SPICE_F32>, grid, dim3(kLogitThreads), 0, s, a, g);
-    } else {
-        const unsigned nb = (unsigned)((a.T + kPrefillTok - 1) / kPrefillTok);
-        if (a.dtype == SPICE_BF16)
-            hipLaunchKernelGGL(route_prefill_kernel<SPICE_BF16>, dim3(nb), dim3(kPrefillThreads), 0, s, a);
-        else
-            hipLaunchKernelGGL(route_prefill_kernel<SPICE_F32>, dim3(nb), dim3(kPrefillThreads), 0, s, a);
-        hipLaunchKernelGGL(bucket_scan_kernel, dim3((unsigned)((3 * a.N + kScanKeys - 1) / kScanKeys)), dim3(kScanThreads),
-                           0, s, a);
-        hipLaunchKernelGGL(bucket_scatter_kernel, dim3(nb), dim3(64), 0, s, a);
+        return hipGetLastError();
     }
+    const int parts = routing_parts(a);
+    const dim3 grid(groups * (unsigned)parts);
+    if (a.T <= kRouteTokenMaxT) {
+        if (a.dtype == SPICE_BF16)
+            hipLaunchKernelGGL((route_tiled_kernel<SPICE_BF16, true>), grid, dim3(kPrefillThreads), 0, s, a, parts);
+        else
+            hipLaunchKernelGGL((route_tiled_kernel<SPICE_F32, true>), grid, dim3(kPrefillThreads), 0, s, a, parts);
+        return hipGetLastError();
+    }
+    if (a.dtype == SPICE_BF16)
+        hipLaunchKernelGGL((route_tiled_kernel<SPICE_BF16, false>), grid, dim3(kPrefillThreads), 0, s, a, parts);
+    else
+        hipLaunchKernelGGL((route_tiled_kernel<SPICE_F32, false>), grid, dim3(kPrefillThreads), 0, s, a, parts);
+    hipLaunchKernelGGL(bucket_scan_kernel, dim3((unsigned)((3 * a.N + kScanKeys - 1) / kScanKeys)), dim3(kScanThreads), 0, s,
+                       a);
+    hipLaunchKernelGGL(bucket_scatter_kernel, dim3(groups), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

@@ -322,8 +322,10 @@ __device__ __forceinline__ int bucket_key(const RouteArgs& a, int s) {
 // LDS of bucket_slots for NT threads: two [NT/64][3N] int tables, the [3N] key totals, a
 // few words and the key cache of `cache` slots (the keys of up to that many slots stay in
 // LDS between the two passes; more slots are read twice).
+constexpr int bucket_misc_ints(int nt) { return nt / 64 > 12 ? 4 + nt / 64 : 16; }
 constexpr size_t bucket_lds_bytes(int nt, int n_experts, int cache) {
-    return (size_t)(2 * (nt / 64) + 1) * 3 * n_experts * sizeof(int) + 16 * sizeof(int) + (size_t)cache * sizeof(int);
+    return (size_t)(2 * (nt / 64) + 1) * 3 * n_experts * sizeof(int) + bucket_misc_ints(nt) * sizeof(int) +
+           (size_t)cache * sizeof(int);
 }
 
 // Stable counting sort of the S = T*K slots by key = class * N + expert, by one block of
@@ -344,7 +346,7 @@ __device__ void bucket_slots(const RouteArgs& a, int* lds) {
     int* s_run = lds + kW * NK;        // [kW][NK]
     int* s_tot = lds + 2 * kW * NK;    // [NK] slots per key
     int* s_misc = s_tot + NK;          // [0..3): class counts, [4..4+kW): wave sums
-    int* s_keys = s_misc + 16;         // [S] when S <= kKeyCache
+    int* s_keys = s_misc + bucket_misc_ints(NT);  // [S] when S <= kKeyCache
     const bool cached = S <= kKeyCache;
     for (int i = tid; i < kW * NK; i += NT) { s_base[i] = 0; s_run[i] = 0; }
     if (tid < 3) s_misc[tid] = 0;

@@ -244,6 +244,7 @@ spice_status_t prep_route(const spice_moe_cfg_t* cfg, int32_t T, const void* x, 
     a.norm_topk = c.norm_topk; a.conf_mode = c.conf_mode; a.tau = c.tau;
     a.x = x; a.wg = w_gate; a.bias = logit_bias; a.resident_slot = resident_slot; a.conf = conf;
     a.logits_out = logits; a.logits_ws = reinterpret_cast<double*>(wsb + L.logits);
+    a.part_ws = reinterpret_cast<double*>(wsb + L.h); a.part_bytes = L.base - L.h;
     a.topk_idx = topk_idx; a.topk_w = topk_w; a.slot_class = slot_class;
     a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
     a.ctrl = reinterpret_cast<uint32_t*>(wsb);

@@ -15,15 +15,16 @@ constexpr int kWordWorkCount = 16;  // [3] non-empty buckets per class (the work
 constexpr int kWordScanCount = 32;  // arrivals of the prefill bucket-scan blocks
 constexpr int kWordRouteDone = 33;  // arrivals of the tokens' last routing blocks (decode routing call)
 constexpr int kWordWorkList = 1024; // [3][N] int4 work records {expert, pool slot, start, n}
-// [T] arrivals of a token's routing blocks (T <= kRouteTokenMaxT), each counter alone in a
+// [T] arrivals of a token's (tiled routing: a 16-token group's) routing blocks, each counter alone in a
 // 128-byte line: the atomics of different tokens' blocks do not queue on one line
 constexpr int kWordTokCount = 4096;
 constexpr int kTokCountStride = 32;  // words between two tokens' counters
 static_assert(kWordWorkList + 3 * SPICE_MAX_EXPERTS * 4 <= kWordTokCount, "work lists overlap the counters");
 
-// Largest T whose routing spreads each token's router rows over a few blocks (larger T:
-// the tiled logits kernel).
+// Largest T whose routing call is one launch.
 constexpr int kRouteTokenMaxT = 256;
+// Fewest tokens whose logits are computed as fp64 MFMA tiles of 16 tokens (route_bucket.hip).
+constexpr int kRouteTiledMinT = 208;
 static_assert((kWordTokCount + kRouteTokenMaxT * kTokCountStride) * 4 <= SPICE_WS_CONTROL_BYTES, "control region too small");
 // [T*K] bucket keys (class * N + expert) of the decode routing call's slots, written through
 // to the device-coherent level for the block that buckets them (top-K of 64 at most)
@@ -65,6 +66,8 @@ struct RouteArgs {
     const float* conf;
     double* logits_out;   // caller's, nullable
     double* logits_ws;    // workspace copy read by the top-K step
+    double* part_ws;      // workspace the FFN uses later: partial logits of the tiled routing
+    size_t part_bytes;    // its size
     int32_t* topk_idx;
     float* topk_w;
     uint8_t* slot_class;
