@@ -46,6 +46,9 @@
 namespace spice {
 namespace {
 
+// Deep is Small's rows halved with eight stages in flight, for up launches whose tiles do not
+// fill the GPU (a draft rollout's shared block and LoRE factors): there a tile waits for its own
+// loads, not for the memory's rate (T = 64: 18.6 -> 14.0 us).
 // Tile shapes: BM weight rows x BT tokens, a grid of WF x WT waves, S stages in LDS, W waves
 // per SIMD the register budget targets, L waves that issue the stages' loads.  Of the big tile's
 // eight waves four load, one per SIMD, so the others' MFMAs never wait behind the load queue
@@ -72,9 +75,10 @@ struct Shape {
     static constexpr int kMxStage = kMxCodes + BT * 256 + kMxScales;
     static constexpr int kMxWLoads = BM / (16 * kWaves), kMxXLoads = BT / (4 * kWaves);  // + 1 of scales
     static constexpr int kLds = S * std::max(kStage, kMxStage);
-    static_assert(kMxWLoads * 16 * kWaves == BM && kMxXLoads * 4 * kWaves == BT && kUpFeat % (16 * kWaves) == 0 &&
-                      (4 * kWaves) % 16 == 0 && BM % 64 == 0 && kWaves % (BM / 64) == 0 && kUpFeat % 64 == 0,
-                  "whole load instructions of whole rows");
+    // whole load instructions of whole rows: the shape can take MXFP4 tiles
+    static constexpr bool kMxOk = kMxWLoads * 16 * kWaves == BM && kMxXLoads * 4 * kWaves == BT &&
+                                  kUpFeat % (16 * kWaves) == 0 && (4 * kWaves) % 16 == 0 && BM % 64 == 0 &&
+                                  kWaves % (BM / 64) == 0 && kUpFeat % 64 == 0;
     static_assert(kRowStep % 16 == 0 && kUpFeat % kRowStep == 0, "staged rows keep their swizzle");
     static_assert(BM % kRowStep == 0 && BT % kRowStep == 0, "whole load instructions");
     static_assert((S - 2) * (kWLoads + kXLoads) < 64, "vmcnt holds the loads in flight");
@@ -82,11 +86,13 @@ struct Shape {
 using Big = Shape<256, 256, 2, 4, 2, 2, 4>;
 using Wide = Shape<256, 128, 4, 2, 3, 2, 8>;
 using Small = Shape<128, 64, 2, 2, 3, 2, 4>;
+using Deep = Shape<64, 64, 2, 2, 8, 2, 4>;
 static_assert(Big::BM == kGemmBigTile[0] && Big::BT == kGemmBigTile[1] && Wide::BM == kGemmWideTile[0] && Wide::BT == kGemmWideTile[1] && Small::BM == kGemmSmallTile[0] &&
                   Small::BT == kGemmSmallTile[1],
               "the shapes' tiles as the split rule knows them");
 
 constexpr int kBK = 64;                          // contraction per stage
+constexpr int kLoreDown = 4;                     // BM-row blocks of a LORE down tile (short: r is small)
 constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;    // an offset past every buffer
 constexpr long long kMaxBuffer = 0xFFFF0000ll;   // bytes a buffer may hold
 constexpr int kRawBufferWord3 = 0x00020000;      // gfx9 raw buffer: 32-bit data format
@@ -175,7 +181,8 @@ __device__ bool resolve(const GemmArgs& a, int L, TileJob& j) {
     const int d = a.d, I = a.I, Is = a.Is;
     const int nt_sh = ((kUp ? Is : d) + feat - 1) / feat;  // weight tiles of the shared block
     const int nt_e = ((kUp ? I : d) + feat - 1) / feat;    // of a routed expert
-    const int nt_l = ((kUp ? a.r : d) + C::BM - 1) / C::BM;  // of a LORE expert
+    constexpr int lrows = kUp ? C::BM : C::BM * kLoreDown;
+    const int nt_l = ((kUp ? a.r : d) + lrows - 1) / lrows;  // of a LORE expert
     const int mt_sh = (a.T + C::BT - 1) / C::BT;
     const int parts = kUp ? 1 : a.parts, per_part = nt_sh * mt_sh;
     const int tiles_sh = Is > 0 ? per_part * parts : 0;
@@ -209,7 +216,7 @@ __device__ bool resolve(const GemmArgs& a, int L, TileJob& j) {
     L -= tiles_sh;
     int e = 0, st = 0, n = 0, slot = -1;
     int kind = kTileHit, nt = nt_e;
-    bool found = a.do_hit && scan_class(a, SPICE_CLASS_HIT, nt_e, C::BT, L, lane, e, st, n, slot);
+    bool found = a.do_hit && a.C > 0 && scan_class(a, SPICE_CLASS_HIT, nt_e, C::BT, L, lane, e, st, n, slot);
     if (!found) {
         kind = kTileLore;
         nt = nt_l;
@@ -245,7 +252,7 @@ __device__ bool resolve(const GemmArgs& a, int L, TileJob& j) {
         j.kdim = kUp ? d : a.r;
         j.nfeat = kUp ? a.r : d;
         j.up_off = C::kUpFeat;  // BM consecutive rows of A
-        j.row0 = nn * C::BM;
+        j.row0 = nn * lrows;
     }
     j.k1 = (j.kdim + kBK - 1) / kBK;
     return true;
@@ -413,16 +420,20 @@ __device__ __forceinline__ int token_row(const GemmArgs& a, const TileJob& j, in
     return s / a.K;
 }
 
-// D = U B_e^T of a LORE tile: BM rows of B_e x BT bucket entries, contraction r.  fp32 MFMAs
+// D = U B_e^T of BM rows of B_e x BT bucket entries (a LORE tile takes kLoreDown such blocks:
+// one alone is shorter than the block's start; draft rollout, T = 64: 17.8 -> 12.7 us), contraction
+// r.  fp32 MFMAs
 // (16x16x4), so that U keeps its 32 bits; operands straight from L2, whose reuse is within the
-// block.  A 16-k step gives each lane 4 consecutive k of its row (quad), and MFMA i takes
-// element i of every lane.  Rows past d and entries past the bucket read the last one.
+// block.  A 32-k step gives each lane 8 consecutive k of its row (quad), and MFMA i takes
+// element i of every lane; the next step's loads are out before this one's MFMAs.  Rows past d
+// and entries past the bucket read the last one.
 template <class C>
 __device__ __forceinline__ void lore_down(const GemmArgs& a, const TileJob& j) {
     const int lane = threadIdx.x & 63, m = lane & 15, quad = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = w % C::WF, wt = w / C::WF;
     const int nlive = min(C::RT, max(0, (j.ntok - j.tok0 - 16 * wt + C::kTStride - 1) / C::kTStride));
+    if (nlive == 0) return;
     const uint16_t* B = static_cast<const uint16_t*>(j.w);
     f32x4_t acc[C::RF][C::RT];
 #pragma unroll
@@ -437,34 +448,43 @@ __device__ __forceinline__ void lore_down(const GemmArgs& a, const TileJob& j) {
 #pragma unroll
     for (int t = 0; t < C::RT; ++t)
         urow[t] = a.u + (size_t)(j.start + min(j.tok0 + t * C::kTStride + wt * 16 + m, j.ntok - 1)) * a.r;
-    for (int k0 = 0; k0 < a.r; k0 += 16) {
-        const int k = k0 + quad * 4;
+    struct Step {
+        u32x4_t b[C::RF];
+        f32x4_t u[C::RT][2];
+    };
+    auto fetch = [&](int k0, Step& st) {
+        const int k = k0 + quad * 8;
         const bool in = k < a.r;  // r is a multiple of 8
-        float av[C::RF][4];
-        f32x4_t bv[C::RT];
+#pragma unroll
+        for (int s = 0; s < C::RF; ++s)
+            st.b[s] = in ? *reinterpret_cast<const u32x4_t*>(brow[s] + k) : u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int t = 0; t < C::RT; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                st.u[t][h] = in && t < nlive ? *reinterpret_cast<const f32x4_t*>(urow[t] + k + 4 * h)
+                                             : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    auto mul = [&](const Step& st) {
 #pragma unroll
         for (int s = 0; s < C::RF; ++s) {
-            uint2 v = {0u, 0u};
-            if (in) v = *reinterpret_cast<const uint2*>(brow[s] + k);
-            av[s][0] = __uint_as_float(v.x << 16);
-            av[s][1] = __uint_as_float(v.x & 0xFFFF0000u);
-            av[s][2] = __uint_as_float(v.y << 16);
-            av[s][3] = __uint_as_float(v.y & 0xFFFF0000u);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t v = st.b[s][i >> 1];
+                const float av = __uint_as_float(i & 1 ? v & 0xFFFF0000u : v << 16);
+#pragma unroll
+                for (int t = 0; t < C::RT; ++t)
+                    if (t < nlive)
+                        acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, st.u[t][i >> 2][i & 3], acc[s][t], 0, 0, 0);
+            }
         }
-#pragma unroll
-        for (int t = 0; t < C::RT; ++t) {
-            bv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            if (in && t < nlive) bv[t] = *reinterpret_cast<const f32x4_t*>(urow[t] + k);
-        }
-#pragma unroll
-        for (int t = 0; t < C::RT; ++t) {
-            if (t >= nlive) continue;
-#pragma unroll
-            for (int s = 0; s < C::RF; ++s)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][i], bv[t][i], acc[s][t], 0, 0, 0);
-        }
+    };
+    Step cur, nxt;
+    fetch(0, cur);
+    for (int k0 = 0; k0 < a.r; k0 += 32) {
+        if (k0 + 32 < a.r) fetch(k0 + 32, nxt);
+        mul(cur);
+        cur = nxt;
     }
 #pragma unroll
     for (int t = 0; t < C::RT; ++t) {
@@ -481,12 +501,13 @@ __device__ __forceinline__ void lore_down(const GemmArgs& a, const TileJob& j) {
 
 template <bool kUp, bool kMx, class C>
 __global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::W))) void expert_gemm_kernel(GemmArgs a) {
+    static_assert(!kMx || C::kMxOk, "MXFP4 tiles need whole load instructions");
     extern __shared__ __align__(16) unsigned char s_lds[];
     TileJob j;
     if (!resolve<kUp, kMx, C>(a, xcd_tile(blockIdx.x, gridDim.x, C::kXcdBlocks), j)) return;
     if constexpr (!kUp) {
         if (j.kind == kTileLore) {
-            lore_down<C>(a, j);
+            for (int b = 0; b < kLoreDown && j.row0 < a.d; ++b, j.row0 += C::BM) lore_down<C>(a, j);
             return;
         }
     }
@@ -723,34 +744,41 @@ void super_shape(int mt, int nt, int most, int* out) {
     out[1] = best_m;
 }
 
-template <bool kMx, class C>
-hipError_t launch_shape(GemmArgs a, bool lore, hipStream_t s) {
-    const long long TK = (long long)a.T * a.K, mt_sh = (a.T + C::BT - 1) / C::BT;
-    auto tiles = [](int n, int per) { return (long long)(n + per - 1) / per; };
-    // upper bounds of the tile counts: sum_e ceil(n_e / BT) <= slots / BT + buckets, the slots of
-    // both classes together at most T K; blocks past the live tiles exit
+long long tiles_of(int n, int per) { return ((long long)n + per - 1) / per; }
+
+// Upper bound of a launch's tiles in shape C: sum_e ceil(n_e / BT) <= slots / BT + buckets, the
+// slots of both classes together at most T K; blocks past the live tiles exit.
+template <bool kUp, class C>
+long long tile_bound(const GemmArgs& a) {
+    const long long TK = (long long)a.T * a.K;
     const long long hit_b = a.do_hit ? std::min<long long>(std::min(a.N, a.C), TK) : 0;
-    const long long lore_b = lore ? std::min<long long>(a.N, TK) : 0;
-    auto bound = [&](long long nt_sh, long long nt_e, long long nt_l, int parts) {
-        return (a.Is > 0 ? mt_sh * nt_sh * parts : 0) + TK / C::BT * std::max(a.do_hit ? nt_e : 0, lore ? nt_l : 0) +
-               hit_b * nt_e + lore_b * nt_l;
-    };
-    const long long up = bound(tiles(a.Is, C::kUpFeat), tiles(a.I, C::kUpFeat), tiles(a.r, C::BM), 1);
-    const long long dn = bound(tiles(a.d, C::BM), tiles(a.d, C::BM), tiles(a.d, C::BM), a.parts);
-    if (up == 0) return hipSuccess;
-    if (up > 0x7FFFFFFFll || dn > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    if (a.Is > 0) {
-        super_shape((int)mt_sh, (int)tiles(a.Is, C::kUpFeat), C::kXcdBlocks, a.super_up);
-        super_shape((int)mt_sh, (int)tiles(a.d, C::BM), C::kXcdBlocks, a.super_dn);
-    }
-    const size_t lds = kMx ? C::kLds : C::S * C::kStage;
-    hipLaunchKernelGGL((expert_gemm_kernel<true, kMx, C>), dim3((unsigned)up), dim3(C::kThreads), lds, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((expert_gemm_kernel<false, kMx, C>), dim3((unsigned)dn), dim3(C::kThreads), lds, s, a);
-    if (a.Is > 0 && a.parts > 1)
-        hipLaunchKernelGGL(shared_sum_kernel, dim3((unsigned)((a.d / 4 + 255) / 256), (unsigned)a.T), dim3(256), 0, s, a.T,
-                           a.d, a.parts, a.part, a.sgate, a.y_shared);
+    const long long lore_b = a.r > 0 ? std::min<long long>(a.N, TK) : 0;
+    const long long nt_sh = kUp ? tiles_of(a.Is, C::kUpFeat) : tiles_of(a.d, C::BM) * a.parts;
+    const long long nt_e = hit_b ? (kUp ? tiles_of(a.I, C::kUpFeat) : tiles_of(a.d, C::BM)) : 0;
+    const long long nt_l = lore_b ? (kUp ? tiles_of(a.r, C::BM) : tiles_of(a.d, C::BM * kLoreDown)) : 0;
+    return (a.Is > 0 ? tiles_of(a.T, C::BT) * nt_sh : 0) + TK / C::BT * std::max(nt_e, nt_l) + hit_b * nt_e + lore_b * nt_l;
+}
+
+template <bool kUp, bool kMx, class C>
+hipError_t launch_pass(GemmArgs a, hipStream_t s) {
+    const long long tiles = tile_bound<kUp, C>(a);
+    if (tiles == 0) return hipSuccess;
+    if (tiles > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    if (a.Is > 0)
+        super_shape((int)tiles_of(a.T, C::BT), (int)(kUp ? tiles_of(a.Is, C::kUpFeat) : tiles_of(a.d, C::BM)), C::kXcdBlocks,
+                    kUp ? a.super_up : a.super_dn);
+    hipLaunchKernelGGL((expert_gemm_kernel<kUp, kMx, C>), dim3((unsigned)tiles), dim3(C::kThreads),
+                       kMx ? C::kLds : C::S * C::kStage, s, a);
+    return hipGetLastError();
+}
+
+template <bool kMx, class Up, class Down>
+hipError_t launch_shapes(const GemmArgs& a, hipStream_t s) {
+    hipError_t e = launch_pass<true, kMx, Up>(a, s);
+    if (e == hipSuccess) e = launch_pass<false, kMx, Down>(a, s);
+    if (e != hipSuccess || a.Is <= 0 || a.parts <= 1) return e;
+    hipLaunchKernelGGL(shared_sum_kernel, dim3((unsigned)((a.d / 4 + 255) / 256), (unsigned)a.T), dim3(256), 0, s, a.T, a.d,
+                       a.parts, a.part, a.sgate, a.y_shared);
     return hipGetLastError();
 }
 
@@ -781,7 +809,7 @@ bool expert_gemm_applies(const FfnArgs& a) {
 }
 
 hipError_t launch_expert_gemm(const FfnArgs& f, bool hit, bool shared, hipStream_t s) {
-    const bool lore = (f.groups & kDoLore) != 0 && f.r > 0;
+    const bool lore = (f.groups & kDoLore) != 0;
     GemmArgs a{};
     a.T = f.T; a.d = f.d; a.N = f.N; a.K = f.K; a.C = f.C; a.I = f.I; a.Is = shared ? f.Is : 0;
     a.r = lore ? f.r : 0;
@@ -808,12 +836,15 @@ hipError_t launch_expert_gemm(const FfnArgs& f, bool hit, bool shared, hipStream
     // MXFP4: two stages of a Big tile would not fit the LDS; a Wide one is the better from twice
     // the bucket on (Small / Wide, us per call: n = 37 215 / 225, n = 73 294 / 261)
     if (f.wfmt == SPICE_WFMT_MXFP4)
-        return gemm_shape(f.T / 2, f.N, f.K) == kGemmSmall ? launch_shape<true, Small>(a, lore, s)
-                                                           : launch_shape<true, Wide>(a, lore, s);
+        return gemm_shape(f.T / 2, f.N, f.K) == kGemmSmall ? launch_shapes<true, Small, Small>(a, s)
+                                                           : launch_shapes<true, Wide, Wide>(a, s);
     switch (gemm_shape(f.T, f.N, f.K)) {
-        case kGemmBig: return launch_shape<false, Big>(a, lore, s);
-        case kGemmWide: return launch_shape<false, Wide>(a, lore, s);
-        default: return launch_shape<false, Small>(a, lore, s);
+        case kGemmBig: return launch_shapes<false, Big, Big>(a, s);
+        case kGemmWide: return launch_shapes<false, Wide, Wide>(a, s);
+        default:
+            // so few tiles that one block per CU holds them all: the deep ring
+            return tile_bound<true, Deep>(a) <= 256 ? launch_shapes<false, Deep, Small>(a, s)
+                                                    : launch_shapes<false, Small, Small>(a, s);
     }
 }
 
