@@ -2,12 +2,11 @@
 prefetch intents.
 
 A rollout starts from the current layer's input hidden state and runs one depth per
-future layer, each depth three library calls on the current stream:
-  route      moe_route_bucket with the future layer's router; every expert is treated as
-             absent with confidence 0 (< tau = 1), so every slot is LoRE and topk_w holds
-             the router's probabilities;
-  surrogate  moe_expert_ffn_grouped with that layer's shared block and LoRE factors:
-             S(h) and B_k A_k h for every predicted expert;
+future layer, each depth two library calls on the current stream:
+  layer      moe_layer_gpu without a combine: the future layer's router with every expert
+             treated as absent with confidence 0 (< tau = 1), so every slot is LoRE and
+             topk_w holds the router's probabilities; beside the routing that layer's shared
+             block, then its LoRE factors: S(h) and B_k A_k h for every predicted expert;
   update     moe_spec_update: enqueue, confidence, halting, draft-state step.
 The predictions land in pinned host memory (written by the update kernel); queue()
 waits for the rollout's event and turns them into per-layer issue lists (Eq. 3).
@@ -74,12 +73,10 @@ class SpecRollout:
             L = layers[j]
             h_in = x if j == 0 else self.state(j - 1)
             h_out = self.state(j)
-            spice.moe_route_bucket(c, T, h_in, L.wg, L.bias, self.resident, self.conf0, None, self.topk_idx,
-                                   self.topk_w, self.slot_class, self.offsets, self.perm, self.inv_perm, None,
-                                   self.ws, self.ws_bytes)
-            spice.moe_expert_ffn_grouped(c, T, h_in, self.perm, self.offsets, self.resident, None, None, L.w13s,
-                                         L.w2s, L.lore_A, L.lore_B, self.y_slots, self.y_shared, self.ws,
-                                         self.ws_bytes)
+            spice.moe_layer_gpu(c, T, h_in, L.wg, L.bias, self.resident, self.conf0, None, None, L.w13s, L.w2s, None,
+                                L.lore_A, L.lore_B, None, self.topk_idx, self.topk_w, self.slot_class, self.offsets,
+                                self.perm, self.inv_perm, self.y_slots, self.y_shared, None, None, None, self.ws,
+                                self.ws_bytes)
             spice.moe_spec_update(c, T, j + 1, l_min, tau, j == n - 1, h_in, h_out, self.topk_idx, self.topk_w,
                                   self.inv_perm, self.y_slots, self.y_shared, self.halted, self.pred_idx[j],
                                   self.pred_prob[j], self.conf[j], self.hosts[j], self.ws, self.ws_bytes)
