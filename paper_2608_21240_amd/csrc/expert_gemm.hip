@@ -356,23 +356,33 @@ __device__ __forceinline__ void product(unsigned char* s_lds, int nk, uint32_t f
 // The main loop of a HIT tile with MXFP4 weights: 128 k per stage.  A lane's 16 code bytes of a
 // row are one block of 32 elements, decoded to the A operands of 4 MFMA steps (v_cvt_scalef32,
 // exact) after they are read from LDS; step u takes elements 8 u .. 8 u + 7 of the lane's block,
-// and the token operand reads the same k (chunk 4 quad + u of its 256-byte row).
+// and the token operand reads the same k (chunk 4 quad + u of its 256-byte row).  load(buf, kt, l)
+// issues the l-th load of a stage: a wave's own loads go out between its MFMAs, not in one run
+// before its fragment reads, where the MFMAs waited for the load queue (T = 777 of
+// DeepSeek-V2-Lite: 242 -> 229 us a call; the bf16 loop, whose stages hold four times the
+// weight bytes, gains nothing from it).  Reading half a stage ahead, as product() does, gave
+// nothing here.
 template <class C, bool kUp, int NL, class Load>
 __device__ __forceinline__ void mx_product(unsigned char* s_lds, int nk, int frow0, int wt, Load load,
                                            f32x4_t (&acc)[C::RF][C::RT]) {
-    constexpr int kLoads = (C::S - 2) * (C::kMxWLoads + C::kMxXLoads + 1);
+    constexpr int kPer = C::kMxWLoads + C::kMxXLoads + 1, kLoads = (C::S - 2) * kPer;
     const int lane = threadIdx.x & 63, m = lane & 15, quad = lane >> 4;
     const uint32_t cbase = (uint32_t)((frow0 + m) * 64 + ((quad ^ ((m >> 2) & 3)) << 4));
     const uint32_t tbase = (uint32_t)(C::kMxCodes + (wt * 16 + m) * 256 + (((4 * quad) ^ m) << 4));
     const uint32_t sbase = (uint32_t)(C::kMxCodes + C::BT * 256 + (frow0 + m) * 4 + quad);
 #pragma unroll
-    for (int s = 0; s < C::S - 1; ++s) load(s, s);
+    for (int s = 0; s < C::S - 1; ++s)
+#pragma unroll
+        for (int l = 0; l < kPer; ++l) load(s, s, l);
     int buf = 0;
     for (int kt = 0; kt < nk; ++kt) {
         // stage kt has landed and every wave has read all of stage kt - 1
         wait_and_barrier<kLoads>();
-        load(buf == 0 ? C::S - 1 : buf - 1, kt + C::S - 1);
-        if constexpr (NL > 0) {
+        const int freed = buf == 0 ? C::S - 1 : buf - 1;
+        if constexpr (NL == 0) {
+#pragma unroll
+            for (int l = 0; l < kPer; ++l) load(freed, kt + C::S - 1, l);
+        } else {
             const unsigned char* base = s_lds + buf * C::kMxStage;
             u32x4_t b[NL][4], raw[C::RF];
             uint32_t sc[C::RF];
@@ -394,12 +404,20 @@ __device__ __forceinline__ void mx_product(unsigned char* s_lds, int nk, int fro
                 u32x4_t op[4];
                 mx_decode(raw[s], e8m0(sc[s]), op);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                    for (int l = 0; l < kPer; ++l)
+                        if (l * 4 * C::RF / kPer == 4 * s + u) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            load(freed, kt + C::S - 1, l);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
 #pragma unroll
                     for (int t = 0; t < NL; ++t)
                         acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, op[u]),
                                                                             __builtin_bit_cast(bf16x8_t, b[t][u]),
                                                                             acc[s][t], 0, 0, 0);
+                }
             }
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
@@ -554,19 +572,20 @@ __global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::
                               : ((uint32_t)(tc >> 3) * (uint32_t)S + (uint32_t)(j.start + pos)) * 128u + (tc & 7) * 16;
         }
         const int nk = j.kdim / 128;
-        auto load = [&](int buf, int kt) {
+        auto load = [&](int buf, int kt, int l) {
             unsigned char* st = s_lds + buf * C::kMxStage;
             const bool in = kt < nk;
-#pragma unroll
-            for (int i = 0; i < C::kMxWLoads; ++i)
-                load_lds16(cbuf, in ? wrow(cr + 16 * C::kWaves * i) * rb + (uint32_t)kt * 64u + cc * 16 : kOutOfRange,
-                           st + (w + C::kWaves * i) * 1024);
-#pragma unroll
-            for (int i = 0; i < C::kMxXLoads; ++i)
+            if (l < C::kMxWLoads) {
+                load_lds16(cbuf, in ? wrow(cr + 16 * C::kWaves * l) * rb + (uint32_t)kt * 64u + cc * 16 : kOutOfRange,
+                           st + (w + C::kWaves * l) * 1024);
+            } else if (l < C::kMxWLoads + C::kMxXLoads) {
+                const int i = l - C::kMxWLoads;
                 load_lds16(xbuf, in && xoff[i] != kOutOfRange ? xoff[i] + (uint32_t)kt * xstep : kOutOfRange,
                            st + C::kMxCodes + (w + C::kWaves * i) * 1024);
-            load_lds4(sbuf, in ? soff + (uint32_t)kt * 4u : kOutOfRange,
-                      st + C::kMxCodes + C::BT * 256 + (w % (C::BM / 64)) * 256);
+            } else {
+                load_lds4(sbuf, in ? soff + (uint32_t)kt * 4u : kOutOfRange,
+                          st + C::kMxCodes + C::BT * 256 + (w % (C::BM / 64)) * 256);
+            }
         };
         if (nlive == C::RT) mx_product<C, kUp, C::RT>(s_lds, nk, frow0, wt, load, acc);
         else if (nlive == 0) mx_product<C, kUp, 0>(s_lds, nk, frow0, wt, load, acc);
