@@ -33,8 +33,14 @@
 // tiles below T = 256 and separate LoRE launches (us per layer call, DeepSeek-V2-Lite sizes):
 // T = 64 204 -> 187, T = 192 259 -> 209, T = 300 311 -> 189, T = 1000 357 -> 263, T = 4096 of
 // Qwen2 3661 -> 3581; Qwen2 T = 96 882 -> 604, T = 300 1325 -> 884 (its shared block split).
-// Tiles: the shared block first, then the HIT experts in id order, then the LORE buckets;
-// inside a group the token tiles of one weight tile are consecutive (the weight tile is then
+// Tiles: the shared block first, then the HIT experts in id order, then the LORE buckets.  In the
+// bf16 shapes with one block per CU (Wide, Big) the reverse: a LORE tile lasts as long as any
+// other (its loads' latency, 27 - 36 us at d = 2048) and was the launch's tail on a fifth of the
+// CUs, and the shared tiles, which L2 feeds, fill the CUs that the last HIT tiles leave
+// (T = 1000 of DeepSeek-V2-Lite 257 -> 242 us a call, T = 2000 367 -> 362, Qwen2 T = 4096 3485 ->
+// 3460).  With two blocks per CU, or MXFP4 tiles, whose weights stream at a lower rate, the shared
+// block first is the better (T = 300 171 / 176, MXFP4 T = 777 229 / 239).
+// Inside a group the token tiles of one weight tile are consecutive (the weight tile is then
 // served from L2), and consecutive tiles are kept on one XCD.
 #include <hip/hip_runtime.h>
 
@@ -67,6 +73,7 @@ struct Shape {
     static constexpr int kStage = (BM + BT) * 128;
     static constexpr int kRowStep = kLoaders / 8;  // rows one load instruction of the loaders covers
     static constexpr int kWLoads = BM / kRowStep, kXLoads = BT / kRowStep;
+    static constexpr bool kOnePerCu = 2 * S * kStage > 163840;
     static constexpr int kXcdBlocks = 32 * std::max(1, 163840 / (S * kStage));  // resident blocks per XCD
     // MXFP4 HIT tiles: 128 k per stage, 64 code bytes and 4 scale bytes per weight row and 256
     // bytes per token row; every wave loads
@@ -188,7 +195,7 @@ __device__ bool resolve(const GemmArgs& a, int L, TileJob& j) {
     const int tiles_sh = Is > 0 ? per_part * parts : 0;
     j.k0 = 0;
     j.part = 0;
-    if (L < tiles_sh) {
+    auto shared_tile = [&](int L) {
         j.part = L / per_part;
         L -= j.part * per_part;
         // groups of sn weight tiles x sm token tiles (about one XCD's worth of blocks)
@@ -212,17 +219,24 @@ __device__ bool resolve(const GemmArgs& a, int L, TileJob& j) {
         j.ntok = a.T;
         j.start = 0;
         return true;
+    };
+    constexpr bool kSharedLast = !kMx && C::kOnePerCu;
+    if constexpr (!kSharedLast) {
+        if (L < tiles_sh) return shared_tile(L);
+        L -= tiles_sh;
     }
-    L -= tiles_sh;
     int e = 0, st = 0, n = 0, slot = -1;
     int kind = kTileHit, nt = nt_e;
-    bool found = a.do_hit && a.C > 0 && scan_class(a, SPICE_CLASS_HIT, nt_e, C::BT, L, lane, e, st, n, slot);
-    if (!found) {
+    auto find_lore = [&]() {
+        if (a.r <= 0 || !scan_class(a, SPICE_CLASS_LORE, nt_l, C::BT, L, lane, e, st, n, slot)) return false;
         kind = kTileLore;
         nt = nt_l;
-        found = a.r > 0 && scan_class(a, SPICE_CLASS_LORE, nt_l, C::BT, L, lane, e, st, n, slot);
-    }
-    if (!found) return false;
+        return true;
+    };
+    bool found = kSharedLast && find_lore();
+    if (!found) found = a.do_hit && a.C > 0 && scan_class(a, SPICE_CLASS_HIT, nt_e, C::BT, L, lane, e, st, n, slot);
+    if (!found && !kSharedLast) found = find_lore();
+    if (!found) return kSharedLast && L < tiles_sh && shared_tile(L);
     if (st < 0 || n <= 0 || st + n > a.T * a.K) {
         if (threadIdx.x == 0) atomicOr(&a.ctrl[kWordFlags], (uint32_t)SPICE_FLAG_BAD_INDEX);
         return false;
