@@ -56,9 +56,9 @@ namespace {
 // fill the GPU (a draft rollout's shared block and LoRE factors): there a tile waits for its own
 // loads, not for the memory's rate (T = 64: 18.6 -> 14.0 us).
 // Tile shapes: BM weight rows x BT tokens, a grid of WF x WT waves, S stages in LDS, W waves
-// per SIMD the register budget targets, L waves that issue the stages' loads.  Of the big tile's
+// per SIMD the register budget targets, L waves that issue the stages' loads.  Of the big tiles'
 // eight waves four load, one per SIMD, so the others' MFMAs never wait behind the load queue
-// (Qwen2, T = 4096: 3764 -> 3633 us).  Measured beside them and slower over their ranges:
+// (Qwen2, T = 4096, Big: 3764 -> 3633 us; T = 1000 of DeepSeek-V2-Lite, Wide: 244 -> 241).  Measured beside them and slower over their ranges:
 // 128 x 128 (2 or 4 stages), 64 x 64, 128 x 32 and 256 x 64 tiles.
 template <int BM_, int BT_, int WF_, int WT_, int S_, int W_, int L_>
 struct Shape {
@@ -91,7 +91,7 @@ struct Shape {
     static_assert((S - 2) * (kWLoads + kXLoads) < 64, "vmcnt holds the loads in flight");
 };
 using Big = Shape<256, 256, 2, 4, 2, 2, 4>;
-using Wide = Shape<256, 128, 4, 2, 3, 2, 8>;
+using Wide = Shape<256, 128, 4, 2, 3, 2, 4>;
 using Small = Shape<128, 64, 2, 2, 3, 2, 4>;
 using Deep = Shape<64, 64, 2, 2, 8, 2, 4>;
 static_assert(Big::BM == kGemmBigTile[0] && Big::BT == kGemmBigTile[1] && Wide::BM == kGemmWideTile[0] && Wide::BT == kGemmWideTile[1] && Small::BM == kGemmSmallTile[0] &&
