@@ -67,7 +67,7 @@ FitLayout fit_layout(const spice_moe_cfg_t& c, int32_t n, int32_t r) {
     FitLayout L{};
     const spice_moe_cfg_t o = one_expert(c);
     size_t off = 0;
-    L.ffn_ws = off;   off += align256(spice::ws_layout(o, n).total);
+    L.ffn_ws = off;   off += align256(spice::ws_layout(o, n).base);  // its FFN does not split the shared block
     L.perm = off;     off += align256((size_t)n * 4);
     L.offsets = off;  off += align256(6 * 4);
     L.resident = off; off += align256(4);

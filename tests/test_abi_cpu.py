@@ -216,3 +216,18 @@ def test_lore_fit_validates_on_the_host():
     assert L.spice_lore_fit_workspace_bytes(ctypes.byref(c), 0, 4) == 0
     assert L.spice_lore_fit_workspace_bytes(ctypes.byref(c), 2000, 4) == 0
     assert L.spice_lore_fit_workspace_bytes(ctypes.byref(c), 512, 32) > 512 * 512 * 16
+
+
+@pytest.mark.parametrize("shape,n,need", [(W.DSV2, 40, 1182208), (W.DSV2, 64, 1836544), (W.DSV2, 512, 17441280),
+                                          (W.QWEN2, 40, 3179008), (W.QWEN2, 512, 43000320)])
+def test_lore_fit_workspace_minimum(shape, n, need):
+    """What a fit needs at the least: the one-expert FFN's buffers without the partial results of a
+    split shared block (which the fit never writes), the targets, the Gram matrices and the
+    coefficients.  The GPU solver's buffers come on top and are optional."""
+    L = spice.lib()
+    c = spice.make_cfg(shape, n_slots=1)
+    D = DUMMY
+    assert L.moe_lore_fit(ctypes.byref(c), n, 32, D, D, D, D, D, D, D, None, None, D, need - 1, None) == \
+        spice.SPICE_ERR_WORKSPACE
+    assert spice.last_error().endswith(f"needs {need}")
+    assert L.spice_lore_fit_workspace_bytes(ctypes.byref(c), n, 32) >= need
