@@ -285,8 +285,15 @@ std::vector<double> singular_values(const std::vector<double>& ev, const std::ve
     return sv;
 }
 
-// The coefficients da, db and the loss with the n x n work on the GPU (gx is only read up to its
-// factor's copy, gy is destroyed).  done = 0 if the iteration does not converge.
+// Waits for the stream on every way out of a scope, exceptions included: declared after the host
+// buffers that queued copies read or write, so that it is gone before they are.
+struct Drain {
+    hipStream_t s;
+    ~Drain() { (void)hipStreamSynchronize(s); }
+};
+
+// The coefficients da, db and the loss with the n x n work on the GPU (gx and gy are destroyed).
+// done = 0 if the iteration does not converge.
 spice_status_t gpu_coefficients(char* w, const FitLayout& L, int32_t n, int32_t r, double* gx, double* gy, double* da,
                                 double* db, uint32_t& flags, double* loss_out, hipError_t e, hipStream_t s, int& done) {
     auto at = [&](size_t off) { return reinterpret_cast<double*>(w + off); };
@@ -296,7 +303,12 @@ spice_status_t gpu_coefficients(char* w, const FitLayout& L, int32_t n, int32_t 
     uint32_t* bad = reinterpret_cast<uint32_t*>(ordd + n);
     auto hip = [](hipError_t x) { return err(SPICE_ERR_HIP, std::string("moe_lore_fit: ") + hipGetErrorString(x)); };
     if (e == hipSuccess) e = spice::launch_fit_tridiag(n, gy, refl, tau, p, dv, ev_, s);
-    std::vector<double> d(n), sub(n);
+    std::vector<double> d, sub, sv, rot[kRotRing];
+    std::vector<int32_t> ord, sw[kRotRing];
+    uint32_t dependent = 0;
+    const Drain drain{s};
+    d.resize(n);
+    sub.resize(n);
     if (e == hipSuccess) e = hipMemcpyAsync(d.data(), dv, (size_t)n * 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(sub.data(), ev_, (size_t)(n - 1) * 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -306,8 +318,6 @@ spice_status_t gpu_coefficients(char* w, const FitLayout& L, int32_t n, int32_t 
     // batches, each copied into its place in the ring
     e = spice::launch_fill_u32(bad, 1, 0u, s);
     if (e == hipSuccess) e = spice::launch_fit_chol(n, gx, chol, bad, s);
-    std::vector<double> rot[kRotRing];
-    std::vector<int32_t> sw[kRotRing];
     int slot = 0;
     bool first = true;
     auto flush = [&]() {
@@ -331,9 +341,8 @@ spice_status_t gpu_coefficients(char* w, const FitLayout& L, int32_t n, int32_t 
         sw[slot].push_back(cnt);
     });
     if (ok) flush();  // with no rotation at all it still writes the identity
-    const std::vector<int32_t> ord = by_size(d);
-    const std::vector<double> sv = singular_values(d, ord, r);
-    uint32_t dependent = 0;
+    ord = by_size(d);
+    sv = singular_values(d, ord, r);
     if (ok && e == hipSuccess) {
         e = hipMemcpyAsync(ordd, ord.data(), (size_t)n * 4, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipMemcpyAsync(svd, sv.data(), (size_t)r * 8, hipMemcpyHostToDevice, s);
@@ -341,7 +350,7 @@ spice_status_t gpu_coefficients(char* w, const FitLayout& L, int32_t n, int32_t 
         if (e == hipSuccess) e = spice::launch_fit_solve(n, r, chol, vec, svd, da, db, s);
         if (e == hipSuccess) e = hipMemcpyAsync(&dependent, bad, 4, hipMemcpyDeviceToHost, s);
     }
-    const hipError_t drained = hipStreamSynchronize(s);  // the host buffers above are read by the copies
+    const hipError_t drained = hipStreamSynchronize(s);
     if (e == hipSuccess) e = drained;
     if (e != hipSuccess) return hip(e);
     if (!ok) return SPICE_OK;
@@ -420,8 +429,9 @@ spice_status_t moe_lore_fit(const spice_moe_cfg_t* cfg, int32_t n, int32_t r, co
         double* da = reinterpret_cast<double*>(w + L.coef_a);
         double* db = reinterpret_cast<double*>(w + L.coef_b);
         uint32_t flags = 0;
+        std::vector<double> ca, cb, hx, hy;
+        const Drain drain{s};
         if (e == hipSuccess) e = hipMemcpyAsync(&flags, fw, 4, hipMemcpyDeviceToHost, s);
-        std::vector<double> ca, cb;  // alive until the copies of them are done
         int done = 0;
         if (n > kFitHostTokens && ws_bytes >= L.total) {
             // on failure to converge (a matrix that is not finite) the host path below decides
@@ -431,7 +441,8 @@ spice_status_t moe_lore_fit(const spice_moe_cfg_t* cfg, int32_t n, int32_t r, co
             if (!done && e == hipSuccess) e = spice::launch_fit_gram(n, d, c.dtype, x, gx, s);
         }
         if (!done) {
-            std::vector<double> hx((size_t)n * n), hy((size_t)n * n);
+            hx.resize((size_t)n * n);
+            hy.resize((size_t)n * n);
             if (e == hipSuccess) e = hipMemcpyAsync(hx.data(), gx, hx.size() * 8, hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipMemcpyAsync(hy.data(), gy, hy.size() * 8, hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -463,7 +474,7 @@ spice_status_t moe_lore_fit(const spice_moe_cfg_t* cfg, int32_t n, int32_t r, co
         if (e == hipSuccess) e = spice::launch_fit_project(n, d, r, c.dtype, x, da, A_out, false, s);
         if (e == hipSuccess) e = spice::launch_fit_project(n, d, r, SPICE_F32, y, db, B_out, true, s);
         if (e == hipSuccess && y_out) e = hipMemcpyAsync(y_out, y, (size_t)n * d * 4, hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host coefficient buffers are read by the copies
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return err(SPICE_ERR_HIP, std::string("moe_lore_fit: ") + hipGetErrorString(e));
         return SPICE_OK;
     } catch (const std::exception& ex) {

@@ -3,9 +3,66 @@
 // built with -fsanitize=address,undefined together with device_stubs.cpp.  Checks on seeded
 // symmetric / SPD matrices of sizes 1..40 (odd and even, for the round-robin bye):
 // A = V diag(w) V^T and V V^T = I to 1e-10, and (L L^T) z = b to 1e-10.  Prints "ok".
-#include "lore_fit.cpp"
+//
+// Then the whole fit against a device of host memory that performs queued copies only when its
+// stream is waited for, with every single allocation of the fit made to fail in turn: no copy may
+// be left that reads or writes the memory of a call that has returned.
+#include <hip/hip_runtime_api.h>
 
 #include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <new>
+
+#include "spice_internal.h"
+
+namespace fake {
+struct Copy {
+    void* to;
+    const void* from;
+    size_t bytes;
+};
+Copy queue[256];
+int queued = 0;
+long fail_after = -1;  // allocations until one fails, or -1
+hipError_t memcpy_async(void* to, const void* from, size_t bytes, hipMemcpyKind, hipStream_t) {
+    if (queued == 256) std::abort();
+    queue[queued++] = Copy{to, from, bytes};
+    return hipSuccess;
+}
+hipError_t synchronize(hipStream_t) {
+    for (int i = 0; i < queued; ++i) std::memcpy(queue[i].to, queue[i].from, queue[i].bytes);
+    queued = 0;
+    return hipSuccess;
+}
+}  // namespace fake
+void* operator new(size_t n) {
+    if (fake::fail_after >= 0 && fake::fail_after-- == 0) throw std::bad_alloc();
+    void* p = std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return std::malloc(n ? n : 1); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+namespace spice {
+template <class... A>
+hipError_t launched(A...) { return hipSuccess; }
+}  // namespace spice
+#define hipMemcpyAsync fake::memcpy_async
+#define hipStreamSynchronize fake::synchronize
+#define launch_fill_u32 launched
+#define launch_expert_ffn launched
+#define launch_fit_setup launched
+#define launch_fit_residual launched
+#define launch_fit_gram launched
+#define launch_fit_project launched
+#define launch_fit_tridiag launched
+#define launch_fit_rotate launched
+#define launch_fit_back launched
+#define launch_fit_chol launched
+#define launch_fit_solve launched
+#include "lore_fit.cpp"
 
 namespace {
 uint64_t g_rng = 0x13198A2E03707344ull;
@@ -15,8 +72,41 @@ double urand() {
 }
 }  // namespace
 
+// The fit of n tokens with its k-th allocation failing, for every k until none is left.
+int failing_allocations(int n) {
+    spice_moe_cfg_t c{};
+    c.d = 512; c.n_experts = 4; c.top_k = 2; c.inter = 8; c.n_slots = 1; c.dtype = SPICE_BF16;
+    const int r = 8;
+    const FitLayout L = fit_layout(c, n, r);
+    std::vector<char> ws(L.total, 0);
+    auto at = [&](size_t off) { return reinterpret_cast<double*>(ws.data() + off); };
+    for (int i = 0; i < n; ++i) {  // Gram matrices, and the tridiagonal form the GPU would leave
+        at(L.gx)[(size_t)i * n + i] = 2.0 + urand();
+        at(L.gy)[(size_t)i * n + i] = 2.0 + urand();
+        if (n > kFitHostTokens) {
+            at(L.small)[3 * n + i] = 2.0 + urand();
+            at(L.small)[4 * n + i] = urand();
+        }
+    }
+    float out = 0.f;
+    double loss = 0.0;
+    for (long k = 0;; ++k) {
+        fake::fail_after = k;
+        const spice_status_t st = moe_lore_fit(&c, n, r, &out, &out, &out, nullptr, nullptr, &out, &out, nullptr, &loss,
+                                               ws.data(), L.total, nullptr);
+        const bool all = fake::fail_after >= 0;
+        fake::fail_after = -1;
+        if (fake::queued != 0 || st != (all ? SPICE_OK : SPICE_ERR_INTERNAL)) {
+            std::fprintf(stderr, "fit of %d tokens, allocation %ld failing: status %d, %d copies left\n", n, k, (int)st,
+                         fake::queued);
+            return 1;
+        }
+        if (all) return k < 5;  // the fit does allocate
+    }
+}
+
 int main() {
-    int fail = 0;
+    int fail = failing_allocations(40) | failing_allocations(64) | failing_allocations(300);
     for (int n : {1, 2, 3, 4, 7, 8, 15, 16, 31, 40}) {
         std::vector<double> a((size_t)n * n);
         for (int i = 0; i < n; ++i)
