@@ -866,12 +866,10 @@ hipError_t launch_expert_gemm(const FfnArgs& f, bool hit, bool shared, hipStream
     a.ctrl = f.ctrl;
     a.part = f.part;
     a.parts = a.Is > 0 && f.part ? gemm_shared_parts(f.T, f.d, f.N, f.K, f.C, f.I, f.Is) : 1;
-    // MXFP4: two stages of a Big tile would not fit the LDS; a Wide one is the better from twice
-    // the bucket on (Small / Wide, us per call: n = 37 215 / 225, n = 73 294 / 261)
+    const int shape = gemm_shape(f.T, f.N, f.K, f.C, f.I, f.Is, f.wfmt);
     if (f.wfmt == SPICE_WFMT_MXFP4)
-        return gemm_shape(f.T / 2, f.N, f.K) == kGemmSmall ? launch_shapes<true, Small, Small>(a, s)
-                                                           : launch_shapes<true, Wide, Wide>(a, s);
-    switch (gemm_shape(f.T, f.N, f.K)) {
+        return shape == kGemmSmall ? launch_shapes<true, Small, Small>(a, s) : launch_shapes<true, Wide, Wide>(a, s);
+    switch (shape) {
         case kGemmBig: return launch_shapes<false, Big, Big>(a, s);
         case kGemmWide: return launch_shapes<false, Wide, Wide>(a, s);
         default:

@@ -182,12 +182,29 @@ inline int gemm_min_tokens(int32_t d, int32_t Is, int32_t wfmt) {
 // once and wastes no token column, and the more weight rows a block takes the more bytes it
 // keeps in flight.  Small / Wide / Big, us per call: n = 18 212 / 216 / 258, n = 48 223 / 211 /
 // 259, n = 94 293 / 266 / 280 (DeepSeek-V2-Lite sizes), n = 128 1774 / 1403 / 1359 (Qwen2).
+// That holds while the tiles fill the GPU (one Wide or Big block per CU); with fewer, a call takes
+// as long as one tile, and the smaller is the shorter.  FFN call, geometric mean over random
+// layers by the up launch's tiles: Wide / Small 1.57 below 64 tiles, 1.38 to 128, 1.22 to 256,
+// about 1.1 to 512; Big / Wide 1.46, 1.34, 1.15, and 1.13 to 384 (at most 3.6 in one layer).
 enum : int { kGemmSmall = 0, kGemmWide = 1, kGemmBig = 2 };
 // weight rows, tokens
 constexpr int kGemmSmallTile[2] = {128, 64}, kGemmWideTile[2] = {256, 128}, kGemmBigTile[2] = {256, 256};
-inline int gemm_shape(int32_t T, int32_t N, int32_t K) {
+constexpr int kGemmWideMinTiles = 320, kGemmBigMinTiles = 256;
+// Up tiles of the shared block and of the HIT buckets, n tokens in each.
+inline int64_t gemm_up_tiles(const int* tile, int32_t T, int64_t n, int32_t N, int32_t C, int32_t I, int32_t Is) {
+    const int64_t feat = tile[0] / 2, buckets = N < C ? N : C, per = n > 0 ? (n + tile[1] - 1) / tile[1] : 1;
+    return ((int64_t)T + tile[1] - 1) / tile[1] * ((Is + feat - 1) / feat) + buckets * per * ((I + feat - 1) / feat);
+}
+// For MXFP4 experts there is no Big shape (two stages of it would not fit the LDS), and Wide is
+// the better from twice the bucket on (Small / Wide, us per call: n = 37 215 / 225, n = 73 294 /
+// 261).
+inline int gemm_shape(int32_t T, int32_t N, int32_t K, int32_t C, int32_t I, int32_t Is, int32_t wfmt) {
     const int64_t n = (int64_t)T * K / (N > 0 ? N : 1);
-    return n < 32 ? kGemmSmall : n < 120 ? kGemmWide : kGemmBig;
+    const bool mx = wfmt == SPICE_WFMT_MXFP4;
+    int s = n < (mx ? 64 : 32) ? kGemmSmall : mx || n < 120 ? kGemmWide : kGemmBig;
+    if (s == kGemmBig && gemm_up_tiles(kGemmBigTile, T, n, N, C, I, Is) < kGemmBigMinTiles) s = kGemmWide;
+    if (s == kGemmWide && gemm_up_tiles(kGemmWideTile, T, n, N, C, I, Is) < kGemmWideMinTiles) s = kGemmSmall;
+    return s;
 }
 // Splits of the shared block's down contraction.  Its tiles are Is / I times as long as a
 // routed expert's; with few of them (small T) the launch would wait for them at its end (Qwen2,
@@ -195,7 +212,7 @@ inline int gemm_shape(int32_t T, int32_t N, int32_t K) {
 // block per CU, two of the others): more only add partial sums (T = 2048: 2117 -> 2166).
 constexpr int kMaxSharedParts = 8;
 inline int gemm_shared_parts(int32_t T, int32_t d, int32_t N, int32_t K, int32_t C, int32_t I, int32_t Is) {
-    const int shape = gemm_shape(T, N, K);
+    const int shape = gemm_shape(T, N, K, C, I, Is, SPICE_WFMT_DTYPE);
     if (T < gemm_min_tokens(d, Is, SPICE_WFMT_DTYPE) || Is <= 0) return 1;
     const int* t = shape == kGemmBig ? kGemmBigTile : shape == kGemmWide ? kGemmWideTile : kGemmSmallTile;
     const int64_t tiles = (int64_t)((T + t[1] - 1) / t[1]) * ((d + t[0] - 1) / t[0]);

@@ -1,0 +1,64 @@
+"""The rules that pick a call's kernels, without a GPU: the inline functions of spice_internal.h
+compiled into a small driver (sanitize/dispatch_driver.cpp), on layers whose best choice was
+measured on a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2608_21240_amd import workloads as W
+
+import test_gpu_gemm as G
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2608_21240_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+SMALL, WIDE, BIG = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block)."""
+    if not shutil.which("g++") or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime_api.h")):
+        pytest.skip("g++ or the HIP headers are not installed")
+    exe = str(tmp_path_factory.mktemp("dispatch") / "driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{ROOT}/include", f"-I{CSRC}", f"-I{ROCM}/include",
+                    "-D__HIP_PLATFORM_AMD__", os.path.join(ROOT, "tests", "sanitize", "dispatch_driver.cpp"), "-o", exe],
+                   check=True)
+
+    def ask(T, s, C, wfmt=0):
+        line = f"{T} {s.d} {s.n_experts} {s.top_k} {C} {s.inter} {s.shared_inter} {wfmt}\n"
+        r = subprocess.run([exe], input=line, capture_output=True, text=True, check=True)
+        return tuple(int(v) for v in r.stdout.split())
+
+    return ask
+
+
+def layer(d, N, K, I, Is, r=16):
+    return W.MoEShape(d=d, n_experts=N, top_k=K, inter=I, shared_inter=Is, lore_rank=r, dtype=W.DTYPE_BF16)
+
+
+# Layers of few tiles, FFN call in us on Small against the shape their buckets' size alone would take:
+# 13.1 / 16.7 and 20.0 / 32.0 (Wide), 71.7 / 102.3 and 30.4 / 42.2 (Wide, Big).
+@pytest.mark.parametrize("T,s,C", [
+    (253, layer(328, 4, 1, 64, 0), 4), (81, layer(1448, 2, 1, 960, 0), 2), (152, layer(1224, 6, 5, 360, 952), 1),
+    (128, layer(256, 16, 4, 256, 384), 8), (81, layer(2576, 3, 3, 280, 0), 3), (600, layer(512, 4, 4, 256, 512), 4)])
+def test_few_tiles_take_the_small_shape(rules, T, s, C):
+    assert T * s.top_k // s.n_experts >= 32
+    assert rules(T, s, C)[0] == SMALL
+
+
+@pytest.mark.parametrize("T,s,C,wfmt,want", [
+    (192, W.DSV2, 48, 0, SMALL), (512, W.DSV2, 48, 0, WIDE), (1000, W.DSV2, 32, 0, WIDE), (1000, W.QWEN2, 64, 0, BIG),
+    (4096, W.QWEN2, 64, 0, BIG), (600, W.DSV2, 64, W.WFMT_MXFP4, SMALL), (777, W.DSV2, 64, W.WFMT_MXFP4, WIDE),
+    (4096, W.QWEN2, 64, W.WFMT_MXFP4, WIDE)])
+def test_large_layers_take_the_shape_of_their_buckets(rules, T, s, C, wfmt, want):
+    assert rules(T, s, C, wfmt)[0] == want
+
+
+def test_the_gpu_cases_reach_the_shapes_they_name(rules):
+    for cases, wfmt, want in ((G.WIDE_TILES, 0, WIDE), (G.BIG_TILES, 0, BIG), (G.MX_WIDE_TILES, W.WFMT_MXFP4, WIDE)):
+        for s, T, R in cases:
+            assert rules(T, s, R, wfmt)[0] == want, (s, T, R)
+    assert rules(96, G.WIDE, 3)[1] == 8

@@ -15,9 +15,10 @@ def shape(d, N, K, I, Is, r):
     return W.MoEShape(d=d, n_experts=N, top_k=K, inter=I, shared_inter=Is, lore_rank=r, dtype=W.DTYPE_BF16)
 
 
-SMALL = shape(200, 20, 5, 104, 168, 24)     # buckets of 16-32: 128 x 64 tiles, k tails of 8 and 40
-WIDE = shape(264, 6, 3, 72, 2064, 136)      # buckets of 32-120, 256 x 128 tiles; shared block split in 8
-BIG = shape(520, 4, 2, 136, 264, 40)        # buckets of 150: 256 x 256 tiles
+# Layers of few tiles: 128 x 64 tiles at any bucket size, 64 x 64 for the up pass
+SMALL = shape(200, 20, 5, 104, 168, 24)     # buckets of 16-32, k tails of 8 and 40
+WIDE = shape(264, 6, 3, 72, 2064, 136)      # buckets of 32-120; shared block split in 8
+BIG = shape(520, 4, 2, 136, 264, 40)        # buckets of 150
 NO_SHARED = shape(256, 8, 2, 128, 0, 16)
 
 
@@ -35,12 +36,28 @@ def test_gemm_edges(s, T, R, gate, fused, layer_call):
     c.check_outputs()
 
 
+# (layer, tokens, residents): enough up tiles for the shapes named, ragged against them
+WIDE_TILES = [(shape(136, 20, 3, 104, 8200, 24), 600, 12), (shape(72, 90, 4, 520, 40, 8), 790, 90)]
+BIG_TILES = [(shape(136, 4, 2, 104, 10960, 40), 600, 3), (shape(264, 64, 4, 520, 0, 8), 2200, 64)]
+MX_WIDE_TILES = [(shape(128, 12, 2, 256, 6920, 24), 705, 10)]
+
+
+@pytest.mark.parametrize("s,T,R", WIDE_TILES + BIG_TILES)
+def test_gemm_tall_tiles(s, T, R):
+    say(f"gemm tall tiles d={s.d} I={s.inter} Is={s.shared_inter} T={T} R={R}")
+    c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=False))
+    c.run_gpu()
+    c.run_oracle(tokens=range(0, T, 3))
+    c.check_routing()
+    c.check_outputs()
+
+
 MX_SMALL = shape(256, 12, 3, 128, 168, 24)  # MXFP4: 2 stages up, 1 down; buckets of 24
-MX_WIDE = shape(384, 6, 3, 256, 1096, 40)   # buckets of 96 and more: 256 x 128 tiles
+MX_WIDE = shape(384, 6, 3, 256, 1096, 40)   # buckets of 96 and more, few tiles
 
 
 @pytest.mark.parametrize("s,T,R", [(MX_SMALL, 71, 12), (MX_SMALL, 72, 5), (MX_SMALL, 97, 12), (MX_WIDE, 200, 3),
-                                   (MX_WIDE, 333, 6)])
+                                   (MX_WIDE, 333, 6)] + MX_WIDE_TILES)
 def test_gemm_mxfp4_edges(s, T, R):
     say(f"gemm mxfp4 d={s.d} I={s.inter} T={T} R={R}")
     c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=True, wfmt=W.WFMT_MXFP4))
