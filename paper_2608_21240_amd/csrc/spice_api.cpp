@@ -577,7 +577,8 @@ spice_status_t moe_layer_gpu(const spice_moe_cfg_t* cfg, int32_t T, const void* 
     const bool gated = w_shared_gate && c.shared_inter > 0;
     hipError_t e;
     if (T <= spice::kRouteTokenMaxT && T * c.top_k <= spice::kLayerMaxSlots &&
-        !spice::expert_gemm_applies(f)) {
+        (!spice::expert_gemm_applies(f) ||
+         spice::layer_fused_is_shorter(T, c.d, c.n_experts, c.top_k, c.shared_inter))) {
         if (gated) {
             float* sg = reinterpret_cast<float*>(static_cast<char*>(ws) + spice::ws_layout(c, T).sgate);
             r.w_sg = w_shared_gate;

@@ -168,15 +168,29 @@ struct CombineArgs {
 // Grouped MFMA GEMMs of the HIT experts, the shared block and the LoRE correction for many
 // tokens (bf16; used by launch_expert_ffn when expert_gemm_applies).
 // Fewest tokens of a call that takes them.  Below, the streaming tiles: one pass over the
-// shared block's weights per 32 tokens, but the routing runs beside the shared block.  Streaming
-// tiles / GEMMs, us per call: DeepSeek-V2-Lite sizes, 48 experts resident, T = 40 177 / 184,
-// T = 64 204 / 187 (8 resident: 88 / 82); Qwen2 sizes, whose shared block is 440 MB, T = 24
-// 310 / 315, T = 32 577 / 549, T = 48 677 / 561.
-// MXFP4 experts: T = 64 115 / 118, T = 96 140 / 125; Qwen2 sizes T = 32 351 / 375, T = 64 483 / 393.
+// shared block's weights per 32 tokens.  Streaming tiles / GEMMs, us per layer call:
+// DeepSeek-V2-Lite sizes, 48 experts resident, T = 40 177 / 184, T = 64 204 / 187 (8 resident: 88 /
+// 82); Qwen2 sizes, whose shared block is 440 MB, T = 24 310 / 315, T = 32 577 / 549, T = 48
+// 677 / 561.  MXFP4 experts, all 64 of DeepSeek-V2-Lite resident: T = 72 145 / 125, T = 96
+// 159 / 131; Qwen2 sizes T = 40 424 / 378, T = 64 482 / 391.
+// Small layers gain nothing from them at so few tokens: layer_fused_is_shorter.
 constexpr int kGemmMinTokens = 64, kGemmMinTokensWide = 32;
 inline int gemm_min_tokens(int32_t d, int32_t Is, int32_t wfmt) {
     const int n = (int64_t)3 * Is * d * 2 >= (64 << 20) ? kGemmMinTokensWide : kGemmMinTokens;
     return wfmt == SPICE_WFMT_MXFP4 ? n + 8 : n;
+}
+// Whether moe_layer_gpu takes the three fused launches where both they and the GEMM tiles could run
+// the call.  The fused launches route beside the shared block's up pass but read a weight once per 32
+// tokens; the GEMMs wait for the routing, and for a shared gate's own launch.  So few slots in short
+// buckets stay fused, as long as the shared block's passes over its rows, T / 32 of d + I_s, are
+// short.  Fused / GEMM, us per call: d = 256, N = 16, K = 4, I = 256, I_s = 384 T = 64 22.1 / 25.8,
+// T = 96 25.5 / 26.6, T = 128 31.5 / 28.0; d = 1024, K = 2, I = 512, I_s = 1024 T = 64 30.0 / 34.7,
+// T = 96 38.0 / 35.4; d = 512, K = 2, I = 512 without a shared block T = 128 20.7 / 26.4, T = 255
+// 28.0 / 31.9.
+inline bool layer_fused_is_shorter(int32_t T, int32_t d, int32_t N, int32_t K, int32_t Is) {
+    const int64_t slots = (int64_t)T * K, n = slots / (N > 0 ? N : 1);
+    if (Is == 0) return slots <= 256 ? n < 64 : slots <= 512 && n < 32;
+    return T <= 96 && slots <= 512 && n < 48 && (int64_t)T * (d + Is) <= 32 * 6000;
 }
 // Tile shape by the mean bucket size: a tile as tall as the buckets are long reads each weight
 // once and wastes no token column, and the more weight rows a block takes the more bytes it

@@ -10,6 +10,7 @@ import pytest
 from paper_2608_21240_amd import workloads as W
 
 import test_gpu_gemm as G
+import test_gpu_layer_limits as LIM
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2608_21240_amd", "csrc")
@@ -19,7 +20,7 @@ SMALL, WIDE, BIG = 0, 1, 2
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block)."""
+    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block, fused layer call)."""
     if not shutil.which("g++") or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime_api.h")):
         pytest.skip("g++ or the HIP headers are not installed")
     exe = str(tmp_path_factory.mktemp("dispatch") / "driver")
@@ -57,8 +58,22 @@ def test_large_layers_take_the_shape_of_their_buckets(rules, T, s, C, wfmt, want
     assert rules(T, s, C, wfmt)[0] == want
 
 
+# Layer calls in us, fused launches / GEMM tiles: 22.1 / 25.8, 30.0 / 34.7, 22.7 / 25.8, 20.7 / 26.4, 28.0 / 31.9,
+# 26.0 / 36.2; 92.3 / 60.5, 155 / 142, 31.5 / 28.0, 47.1 / 35.5, 577 / 549.
+@pytest.mark.parametrize("T,s,fused", [
+    (64, layer(256, 16, 4, 256, 384), 1), (64, layer(1024, 16, 2, 512, 1024), 1), (64, layer(128, 64, 6, 64, 128), 1),
+    (128, layer(512, 16, 2, 512, 0), 1), (255, layer(512, 16, 2, 512, 0), 1), (133, layer(896, 21, 1, 1336, 0), 1),
+    (128, layer(2048, 16, 2, 1408, 2816), 0), (64, W.DSV2, 0), (128, layer(256, 16, 4, 256, 384), 0),
+    (128, layer(1024, 16, 2, 512, 1024), 0), (32, W.QWEN2, 0)])
+def test_small_layers_keep_the_fused_launches(rules, T, s, fused):
+    assert rules(T, s, s.n_experts // 2)[2] == fused
+
+
 def test_the_gpu_cases_reach_the_shapes_they_name(rules):
     for cases, wfmt, want in ((G.WIDE_TILES, 0, WIDE), (G.BIG_TILES, 0, BIG), (G.MX_WIDE_TILES, W.WFMT_MXFP4, WIDE)):
         for s, T, R in cases:
             assert rules(T, s, R, wfmt)[0] == want, (s, T, R)
     assert rules(96, G.WIDE, 3)[1] == 8
+    for s, T, fused in ((LIM.SMALL, 64, 1), (LIM.SMALL, 96, 1), (LIM.SMALL, 97, 0), (LIM.LONG, 64, 0), (LIM.NO_SHARED, 255, 1),
+                        (LIM.NO_SHARED, 257, 0), (LIM.MX_GEMM, 97, 0)):
+        assert rules(T, s, 7)[2] == fused, (s, T)
