@@ -819,6 +819,7 @@ hipError_t launch_shapes(const GemmArgs& a, hipStream_t s) {
 
 bool expert_gemm_applies(const FfnArgs& a) {
     if (a.dtype != SPICE_BF16 || a.T < gemm_min_tokens(a.d, a.Is, a.wfmt)) return false;
+    if (!(a.groups & (kDoHit | kDoShared)) && !lore_gemm_is_shorter(a.T, a.d, a.N, a.K)) return false;
     // offsets inside one operand are 32-bit
     auto fits = [](long long rows, long long cols) { return rows * ((cols + kBK - 1) / kBK * kBK) * 2 <= kMaxBuffer; };
     // MXFP4 blocks of whole stages and 16-byte rows of codes
@@ -866,7 +867,7 @@ hipError_t launch_expert_gemm(const FfnArgs& f, bool hit, bool shared, hipStream
     a.ctrl = f.ctrl;
     a.part = f.part;
     a.parts = a.Is > 0 && f.part ? gemm_shared_parts(f.T, f.d, f.N, f.K, f.C, f.I, f.Is) : 1;
-    const int shape = gemm_shape(f.T, f.N, f.K, f.C, f.I, f.Is, f.wfmt);
+    const int shape = gemm_shape(f.T, f.N, f.K, hit ? f.C : 0, f.I, a.Is, f.wfmt);
     if (f.wfmt == SPICE_WFMT_MXFP4)
         return shape == kGemmSmall ? launch_shapes<true, Small, Small>(a, s) : launch_shapes<true, Wide, Wide>(a, s);
     switch (shape) {

@@ -192,6 +192,15 @@ inline bool layer_fused_is_shorter(int32_t T, int32_t d, int32_t N, int32_t K, i
     if (Is == 0) return slots <= 256 ? n < 64 : slots <= 512 && n < 32;
     return T <= 96 && slots <= 512 && n < 48 && (int64_t)T * (d + Is) <= 32 * 6000;
 }
+// Whether the LoRE corrections alone (lore_surrogate_apply) take the GEMM tiles.  A tile waits for d /
+// 64 stages one after the other, the streaming tiles read the factors once per 32 entries of a
+// bucket: GEMM / streaming, geometric mean over random layers at d = 2048 - 4096 1.57 times with
+// 4 - 8 entries in the mean bucket, 1.00 with 16 - 32, 0.63 with 64 - 128; at d = 256 - 512 1.07,
+// 0.83, 0.40.  (Buckets that residents leave short keep the GEMMs, up to twice as long.)
+inline bool lore_gemm_is_shorter(int32_t T, int32_t d, int32_t N, int32_t K) {
+    const int64_t n = (int64_t)T * K / (N > 0 ? N : 1);
+    return n >= 16 && 28 * n >= d;
+}
 // Tile shape by the mean bucket size: a tile as tall as the buckets are long reads each weight
 // once and wastes no token column, and the more weight rows a block takes the more bytes it
 // keeps in flight.  Small / Wide / Big, us per call: n = 18 212 / 216 / 258, n = 48 223 / 211 /

@@ -20,7 +20,8 @@ SMALL, WIDE, BIG = 0, 1, 2
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block, fused layer call)."""
+    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block, fused layer call, GEMM tiles for LoRE
+    alone)."""
     if not shutil.which("g++") or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime_api.h")):
         pytest.skip("g++ or the HIP headers are not installed")
     exe = str(tmp_path_factory.mktemp("dispatch") / "driver")
@@ -69,6 +70,16 @@ def test_small_layers_keep_the_fused_launches(rules, T, s, fused):
     assert rules(T, s, s.n_experts // 2)[2] == fused
 
 
+# lore_surrogate_apply in us, streaming / GEMM tiles: 12.0 / 26.2, 13.0 / 29.9, 13.9 / 30.1, 10.3 / 21.5; 107.4 / 11.8,
+# 22.9 / 11.0, 50.6 / 16.7, 243.7 / 65.5.
+@pytest.mark.parametrize("T,s,gemm", [
+    (71, layer(3968, 49, 1, 64, 64, 16), 0), (120, layer(3496, 99, 3, 64, 64, 40), 0), (193, layer(3968, 51, 3, 64, 64, 56), 0),
+    (64, W.DSV2, 0), (182, layer(80, 73, 8, 64, 64, 64), 1), (142, layer(128, 31, 7, 64, 64, 40), 1),
+    (108, layer(112, 3, 2, 64, 64, 64), 1), (498, layer(3200, 7, 7, 64, 64, 16), 1)])
+def test_lore_alone_takes_the_shorter_tiles(rules, T, s, gemm):
+    assert rules(T, s, 1)[3] == gemm
+
+
 def test_the_gpu_cases_reach_the_shapes_they_name(rules):
     for cases, wfmt, want in ((G.WIDE_TILES, 0, WIDE), (G.BIG_TILES, 0, BIG), (G.MX_WIDE_TILES, W.WFMT_MXFP4, WIDE)):
         for s, T, R in cases:
@@ -77,3 +88,4 @@ def test_the_gpu_cases_reach_the_shapes_they_name(rules):
     for s, T, fused in ((LIM.SMALL, 64, 1), (LIM.SMALL, 96, 1), (LIM.SMALL, 97, 0), (LIM.LONG, 64, 0), (LIM.NO_SHARED, 255, 1),
                         (LIM.NO_SHARED, 257, 0), (LIM.MX_GEMM, 97, 0)):
         assert rules(T, s, 7)[2] == fused, (s, T)
+    assert [rules(T, s, 1)[3] for s, T in ((G.SMALL, 130), (G.NO_SHARED, 64), (G.SPARSE, 130))] == [1, 1, 0]

@@ -20,13 +20,15 @@ SMALL = shape(200, 20, 5, 104, 168, 24)     # buckets of 16-32, k tails of 8 and
 WIDE = shape(264, 6, 3, 72, 2064, 136)      # buckets of 32-120; shared block split in 8
 BIG = shape(520, 4, 2, 136, 264, 40)        # buckets of 150
 NO_SHARED = shape(256, 8, 2, 128, 0, 16)
+SPARSE = shape(520, 64, 3, 72, 104, 40)     # buckets of 6: LoRE alone stays on the streaming tiles
 
 
 @pytest.mark.parametrize("layer_call", [True, False])
 @pytest.mark.parametrize("s,T,R,gate,fused", [
     (SMALL, 63, 9, False, True), (SMALL, 64, 9, False, True), (SMALL, 65, 20, True, True),
     (SMALL, 130, 3, False, False), (WIDE, 96, 3, True, True), (WIDE, 209, 2, False, True), (BIG, 300, 2, False, True),
-    (BIG, 257, 4, True, True), (NO_SHARED, 129, 4, False, True), (NO_SHARED, 64, 1, False, False)])
+    (BIG, 257, 4, True, True), (NO_SHARED, 129, 4, False, True), (NO_SHARED, 64, 1, False, False),
+    (SPARSE, 130, 20, False, False)])
 def test_gemm_edges(s, T, R, gate, fused, layer_call):
     say(f"gemm d={s.d} I={s.inter} Is={s.shared_inter} T={T} R={R} gate={gate} fused={fused}")
     c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=True, shared_gate=gate))
