@@ -1,14 +1,14 @@
 // Router logits, softmax top-K gating, per-slot classification and (class, expert)
 // bucketing (Eq. 1; Sec. 2.1, 4.2, 4.3).  No block waits for another block.
 //
-// T < kRouteTiledMinT (decode), one launch (route_logits_kernel): a token's router rows
+// Few tokens (route_keeps_rows), one launch (route_logits_kernel): a token's router rows
 //   are spread over several blocks (one row per wave), each summing its logits in fp64; the
 //   last of the token's blocks to finish (an arrival counter per token) takes the token's
 //   top-K, gates, confidence and classes and publishes them, with the slots' bucket keys,
 //   at the device-coherent level; the last of those blocks over all tokens (a second
 //   arrival counter) sorts the T*K slots by (class, expert), writes the work lists and,
 //   when asked, the CPU path's host copies and their ready word.
-// Up to kRouteTokenMaxT, one launch of route_tiled_kernel: per 16 tokens, the logits as fp64
+// Else up to kRouteTokenMaxT, one launch of route_tiled_kernel: per 16 tokens, the logits as fp64
 //   MFMA tiles of 16 experts x 16 tokens, the contraction split over several blocks whose
 //   last one adds their partial logits in order and takes the tokens' top-K, gates and
 //   classes; the last block over all tokens buckets the slots as above.
@@ -22,8 +22,7 @@
 // The tiled logits are bound by the fp64 matrix rate of the CUs that hold a block: with a block
 // per 16 tokens, 63 CUs at T = 1000; with the contraction split, all 256 (N = 64, d = 2048: the
 // three launches 40 -> 26 us).  Below kRouteTiledMinT the row-per-wave launch is shorter (rows /
-// tiles, us per call: T = 64 12.1 / 20.6, T = 192 20.3 / 21.6, T = 256 24.4 / 21.7; at d = 3584
-// T = 192 24.7 / 21.7).
+// tiles, us per call at N = 64: T = 64 12.1 / 20.6, T = 192 20.3 / 21.6, T = 256 24.4 / 21.7).
 //
 // bf16 x bf16 and fp32 x fp32 products are exact in fp64, so on every path only the
 // summation order of the logits differs from a plain loop.
@@ -64,8 +63,8 @@ __global__ __launch_bounds__(kLogitThreads) void route_logits_kernel(RouteArgs a
 
 constexpr int kPrefillThreads = 1024;  // 16 waves
 constexpr int kGroupTiles = 2;          // expert tiles of 16 per routing wave
-constexpr int kPrefillTok = 16;       // tokens per prefill routing block (one MFMA tile wide)
-constexpr int kMaxParts = 8;          // contraction parts of a tiled routing group, a block each
+constexpr int kPrefillTok = kRouteTileTok;  // tokens per prefill routing block (one MFMA tile wide)
+constexpr int kMaxParts = kRouteMaxParts;   // contraction parts of a tiled routing group, a block each
 constexpr int kScanThreads = 1024;    // bucket_scan_kernel: a wave per key; the last block a thread per key
 constexpr int kScanKeys = kScanThreads / 64;  // bucket keys per scan block
 static_assert(3 * SPICE_MAX_EXPERTS <= kScanThreads, "a scan thread per bucket key");
@@ -438,21 +437,10 @@ __global__ __launch_bounds__(64) void bucket_scatter_kernel(RouteArgs a) {
 
 }  // namespace
 
-// Contraction parts per group of 16 tokens: as many as fill the 256 CUs with a block each (a
-// group's logits are bound by its CU's fp64 matrix rate), at least two 64- or 32-wide passes
-// per part, and partial logits that fit the workspace.
-static int routing_parts(const RouteArgs& a) {
-    const int groups = (a.T + kPrefillTok - 1) / kPrefillTok;
-    const int npass = a.d * (a.dtype == SPICE_BF16 ? 2 : 4) / 128;
-    const size_t per_part = (size_t)groups * kPrefillTok * a.N * sizeof(double);
-    int p = std::min({kMaxParts, 256 / groups, npass / 2});
-    if ((size_t)std::max(p, 0) * per_part > a.part_bytes) p = (int)(a.part_bytes / per_part);
-    return std::max(p, 1);
-}
-
 hipError_t launch_route_bucket(const RouteArgs& a, hipStream_t s) {
     const unsigned groups = (unsigned)((a.T + kPrefillTok - 1) / kPrefillTok);
-    if (a.T < kRouteTiledMinT) {
+    const int parts = route_parts(a.T, a.N, a.d, a.dtype, a.part_bytes);
+    if (route_keeps_rows(a.T, a.N, a.d, parts, a.hx != nullptr)) {
         const int g = route_blocks_per_token(a.N + (a.w_sg ? 1 : 0), kLogitThreads);
         const dim3 grid((unsigned)(a.T * g));
         if (a.dtype == SPICE_BF16)
@@ -461,7 +449,6 @@ hipError_t launch_route_bucket(const RouteArgs& a, hipStream_t s) {
             hipLaunchKernelGGL(route_logits_kernel<SPICE_F32>, grid, dim3(kLogitThreads), 0, s, a, g);
         return hipGetLastError();
     }
-    const int parts = routing_parts(a);
     const dim3 grid(groups * (unsigned)parts);
     if (a.T <= kRouteTokenMaxT) {
         if (a.dtype == SPICE_BF16)

@@ -23,8 +23,36 @@ static_assert(kWordWorkList + 3 * SPICE_MAX_EXPERTS * 4 <= kWordTokCount, "work 
 
 // Largest T whose routing call is one launch.
 constexpr int kRouteTokenMaxT = 256;
-// Fewest tokens whose logits are computed as fp64 MFMA tiles of 16 tokens (route_bucket.hip).
+// Fewest tokens whose logits may be computed as fp64 MFMA tiles of 16 tokens (route_bucket.hip).
 constexpr int kRouteTiledMinT = 208;
+// Contraction parts per group of 16 tokens of the tiled logits: as many as fill the 256 CUs with a
+// block each (a group's logits are bound by its CU's fp64 matrix rate), at least two passes of
+// 128 bytes per part, and partial logits that fit part_bytes.  One for small products, whose logits
+// take less time than a group's wait for its parts (whole / split: N = 12, d = 144 15.2 / 16.6 us,
+// N = 64, d = 256 22.4 / 24.6; N = 5, d = 3736 23.1 / 17.4, N = 35, d = 1440 26.4 / 21.2).
+constexpr int kRouteTileTok = 16, kRouteMaxParts = 8;
+inline int route_parts(int32_t T, int32_t N, int32_t d, int32_t dtype, size_t part_bytes) {
+    if ((int64_t)N * d < (d <= 1024 ? 24000 : 12000)) return 1;
+    const int groups = (T + kRouteTileTok - 1) / kRouteTileTok;
+    const int npass = d * (dtype == SPICE_BF16 ? 2 : 4) / 128;
+    const size_t per_part = (size_t)groups * kRouteTileTok * N * sizeof(double);
+    int p = kRouteMaxParts;
+    p = p < 256 / groups ? p : 256 / groups;
+    p = p < npass / 2 ? p : npass / 2;
+    if ((size_t)(p > 0 ? p : 0) * per_part > part_bytes) p = (int)(part_bytes / per_part);
+    return p > 1 ? p : 1;
+}
+// Whether a routing call of kRouteTiledMinT tokens or more keeps a row per wave (kRouteTokenMaxT at
+// most).  The tiles pay for many experts whose contraction is split far enough; copying x to the host
+// the last block's 1024 threads take less time than the rows' 256, unless the logits take very long.
+// Rows / tiles, us per call of 208 - 256 tokens: N = 17, d = 2048 13.0 / 18.4; N = 64, d = 2048 in 8
+// parts 24.4 / 21.7; N = 128, d = 4096 in one part 49.6 / 94.2; with x to the host N = 28, d = 2040
+// 58 / 43, N = 256, d = 4096 in one part 197 / 249.
+inline bool route_keeps_rows(int32_t T, int32_t N, int32_t d, int parts, bool x_to_host) {
+    if (T < kRouteTiledMinT) return true;
+    if (T > kRouteTokenMaxT) return false;
+    return x_to_host ? N >= 128 && d > 16 * T * parts : N < 56 || d > 4 * T * parts;
+}
 static_assert((kWordTokCount + kRouteTokenMaxT * kTokCountStride) * 4 <= SPICE_WS_CONTROL_BYTES, "control region too small");
 // [T*K] bucket keys (class * N + expert) of the decode routing call's slots, written through
 // to the device-coherent level for the block that buckets them (top-K of 64 at most)

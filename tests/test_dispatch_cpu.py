@@ -19,19 +19,24 @@ SMALL, WIDE, BIG = 0, 1, 2
 
 
 @pytest.fixture(scope="module")
-def rules(tmp_path_factory):
-    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block, fused layer call, GEMM tiles for LoRE
-    alone)."""
+def driver(tmp_path_factory):
     if not shutil.which("g++") or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime_api.h")):
         pytest.skip("g++ or the HIP headers are not installed")
     exe = str(tmp_path_factory.mktemp("dispatch") / "driver")
     subprocess.run(["g++", "-std=c++17", "-O1", f"-I{ROOT}/include", f"-I{CSRC}", f"-I{ROCM}/include",
                     "-D__HIP_PLATFORM_AMD__", os.path.join(ROOT, "tests", "sanitize", "dispatch_driver.cpp"), "-o", exe],
                    check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def rules(driver):
+    """rules(T, shape, C, wfmt=0) -> (tile shape, parts of the shared block, fused layer call, GEMM tiles for LoRE
+    alone)."""
 
     def ask(T, s, C, wfmt=0):
         line = f"{T} {s.d} {s.n_experts} {s.top_k} {C} {s.inter} {s.shared_inter} {wfmt}\n"
-        r = subprocess.run([exe], input=line, capture_output=True, text=True, check=True)
+        r = subprocess.run([driver], input=line, capture_output=True, text=True, check=True)
         return tuple(int(v) for v in r.stdout.split())
 
     return ask
@@ -39,6 +44,18 @@ def rules(tmp_path_factory):
 
 def layer(d, N, K, I, Is, r=16):
     return W.MoEShape(d=d, n_experts=N, top_k=K, inter=I, shared_inter=Is, lore_rank=r, dtype=W.DTYPE_BF16)
+
+
+@pytest.fixture(scope="module")
+def routing(driver):
+    """routing(T, N, d, dtype, part_bytes, x_to_host) -> (contraction parts, row per wave)."""
+
+    def ask(*args):
+        r = subprocess.run([driver, "routing"], input=" ".join(str(int(v)) for v in args) + "\n", capture_output=True,
+                           text=True, check=True)
+        return tuple(int(v) for v in r.stdout.split())
+
+    return ask
 
 
 # Layers of few tiles, FFN call in us on Small against the shape their buckets' size alone would take:
@@ -78,6 +95,27 @@ def test_small_layers_keep_the_fused_launches(rules, T, s, fused):
     (108, layer(112, 3, 2, 64, 64, 64), 1), (498, layer(3200, 7, 7, 64, 64, 16), 1)])
 def test_lore_alone_takes_the_shorter_tiles(rules, T, s, gemm):
     assert rules(T, s, 1)[3] == gemm
+
+
+# moe_route_bucket in us, row per wave / tiles: 13.0 / 18.4, 12.1 / 14.5, 49.6 / 94.2 (a workspace with room for one
+# part), 197 / 249 (the same, with x to the host), 24.4 / 21.7, 26.0 / 22; with x to the
+# host 58 / 43.
+@pytest.mark.parametrize("T,N,d,room,x_to_host,rows", [
+    (208, 17, 2048, 1 << 30, 0, 1), (208, 8, 256, 1 << 30, 0, 1), (208, 128, 4096, 300000, 0, 1),
+    (208, 256, 4096, 700000, 1, 1), (256, 64, 2048, 1 << 30, 0, 0), (256, 64, 3584, 1 << 30, 0, 0), (208, 28, 2040, 1 << 30, 1, 0),
+    (207, 64, 2048, 1 << 30, 0, 1), (207, 64, 2048, 1 << 30, 1, 1), (257, 8, 64, 1 << 30, 0, 0)])
+def test_routing_keeps_rows_where_they_are_shorter(routing, T, N, d, room, x_to_host, rows):
+    assert routing(T, N, d, W.DTYPE_BF16, room, x_to_host)[1] == rows
+
+
+# Small products stay whole (15.2 / 16.6 us in two parts, 15.6 / 18.1, 22.4 / 24.6); large ones are split, as far as the
+# workspace, the CUs and the passes go.
+@pytest.mark.parametrize("T,N,d,dtype,room,parts", [
+    (563, 12, 144, W.DTYPE_F32, 1 << 30, 1), (1172, 8, 448, W.DTYPE_BF16, 1 << 30, 1), (388, 35, 1440, W.DTYPE_BF16, 1 << 30, 8),
+    (1000, 64, 2048, W.DTYPE_BF16, 1 << 30, 4), (1000, 64, 2048, W.DTYPE_BF16, 3 * 63 * 16 * 64 * 8, 3),
+    (1000, 64, 2048, W.DTYPE_BF16, 0, 1), (4096, 64, 2048, W.DTYPE_BF16, 1 << 30, 1), (300, 64, 256, W.DTYPE_BF16, 1 << 30, 1), (300, 64, 384, W.DTYPE_BF16, 1 << 30, 3)])
+def test_routing_parts(routing, T, N, d, dtype, room, parts):
+    assert routing(T, N, d, dtype, room, 0)[0] == parts
 
 
 def test_the_gpu_cases_reach_the_shapes_they_name(rules):

@@ -39,3 +39,17 @@ def test_tiled_routing(s, T, R):
         assert np.array_equal(to_np(c.run.topk_idx), c.o["idx"]) and np.array_equal(to_np(c.run.perm), c.o["perm"])
         assert np.array_equal(c.run.idx_host.numpy(), c.o["idx"]) and np.array_equal(c.run.cls_host.numpy(), c.o["cls"])
         assert np.array_equal(to_np(c.run.x_host), c.x)
+
+
+# without host copies: few experts, or a contraction split too little for its length, stay on the
+# row-per-wave launch up to 256 tokens; one part for a small product
+@pytest.mark.parametrize("s,T,R", [
+    (shape(2048, 55, 6, BF), 208, 20), (shape(2048, 56, 6, BF, I=512), 208, 20), (shape(2048, 56, 6, BF, I=512), 207, 20),
+    (shape(4096, 128, 2, BF), 256, 20), (shape(4096, 128, 2, BF), 257, 20), (shape(1024, 100, 8, F32), 256, 31),
+    (shape(136, 87, 3, BF), 300, 9), (shape(256, 93, 3, F32, I=256), 300, 9), (shape(256, 95, 3, F32, I=256), 300, 9)])
+def test_routing_without_host_copies(s, T, R):
+    say(f"routing on the device alone d={s.d} N={s.n_experts} K={s.top_k} T={T} R={R} dtype={s.dtype}")
+    c = Case(W.Workload("route", s, tokens=T, resident=R, skew=True))
+    c.run_gpu(exact=False, layer_call=False)
+    c.run_oracle(tokens=[0, T - 1])
+    c.check_routing()
