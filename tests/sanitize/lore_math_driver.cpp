@@ -1,8 +1,10 @@
 // Sanitizer driver for the host linear algebra of the LoRE fit (lore_fit.cpp's Jacobi
-// eigensolver and Cholesky solve), included here so its internal functions are reachable;
-// built with -fsanitize=address,undefined together with device_stubs.cpp.  Checks on seeded
+// eigensolver, QR iteration and Cholesky solve), included here so its internal functions are
+// reachable; built with -fsanitize=address,undefined together with device_stubs.cpp.  Checks on seeded
 // symmetric / SPD matrices of sizes 1..40 (odd and even, for the round-robin bye):
-// A = V diag(w) V^T and V V^T = I to 1e-10, and (L L^T) z = b to 1e-10.  Prints "ok".
+// A = V diag(w) V^T and V V^T = I to 1e-10, and (L L^T) z = b to 1e-10; and the same of
+// tridiagonal matrices up to 300 (random, graded, clustered, split, zero, with entries that are
+// not finite) under the rotations that tridiag_qr hands out.  Prints "ok".
 //
 // Then the whole fit against a device of host memory that performs queued copies only when its
 // stream is waited for, with every single allocation of the fit made to fail in turn: no copy may
@@ -105,8 +107,80 @@ int failing_allocations(int n) {
     }
 }
 
+// T = Z^T diag(w) Z with the rows z_k of Z turned by the rotations handed out, for the tridiagonal
+// matrix with diagonal d and subdiagonal e; rounding of n rotations per sweep and about two sweeps
+// per eigenvalue: 4 n^1.5 units of 2^-53 of the largest entry bound both residuals.
+int tridiag_case(const char* name, int n, std::vector<double> d, std::vector<double> e) {
+    const std::vector<double> d0 = d, e0 = e;
+    std::vector<double> z((size_t)n * n, 0.0);
+    for (int i = 0; i < n; ++i) z[(size_t)i * n + i] = 1.0;
+    long planes = 0;
+    const bool ok = tridiag_qr(n, d, e, [&](int lo, int cnt, const std::vector<double>& cs) {
+        if (lo < 0 || cnt < 1 || lo + cnt >= n || cs.size() != 2 * (size_t)cnt) std::abort();
+        planes += cnt;
+        for (int k = 0; k < cnt; ++k)
+            for (int i = 0; i < n; ++i) {
+                double &a = z[(size_t)(lo + k) * n + i], &b = z[(size_t)(lo + k + 1) * n + i];
+                const double x = a, y = b, c = cs[2 * k], s = cs[2 * k + 1];
+                a = c * x + s * y;
+                b = c * y - s * x;
+            }
+    });
+    double scale = 1e-300, res = 0.0, orth = 0.0;
+    for (int i = 0; i < n; ++i) scale = std::fmax(scale, std::fmax(std::fabs(d0[i]), i + 1 < n ? std::fabs(e0[i]) : 0.0));
+    for (int i = 0; ok && i < n; ++i)
+        for (int j = 0; j <= i; ++j) {
+            double t = 0.0, o = 0.0;
+            for (int k = 0; k < n; ++k) {
+                t += z[(size_t)k * n + i] * d[k] * z[(size_t)k * n + j];
+                o += z[(size_t)i * n + k] * z[(size_t)j * n + k];
+            }
+            const double want = i == j ? d0[i] : i == j + 1 ? e0[j] : 0.0;
+            res = std::fmax(res, std::fabs(t - want) / scale);
+            orth = std::fmax(orth, std::fabs(o - (i == j ? 1.0 : 0.0)));
+        }
+    const double bound = 4.0 * n * std::sqrt((double)n) * 1.2e-16 + 1e-15;
+    if (ok && res <= bound && orth <= bound) return 0;
+    std::fprintf(stderr, "tridiag %s n=%d: %s, residual %.2e, orthogonality %.2e, %ld rotations\n", name, n,
+                 ok ? "converged" : "no convergence", res, orth, planes);
+    return 1;
+}
+
+int tridiagonal() {
+    int fail = 0;
+    for (int n : {1, 2, 3, 49, 64, 150, 300}) {
+        std::vector<double> d(n), e(n > 1 ? n - 1 : 0);
+        auto fill = [&](auto f, auto g) {
+            for (int i = 0; i < n; ++i) d[i] = f(i);
+            for (int i = 0; i + 1 < n; ++i) e[i] = g(i);
+        };
+        fill([&](int) { return urand(); }, [&](int) { return urand(); });
+        fail |= tridiag_case("random", n, d, e);
+        fill([&](int i) { return std::pow(0.8, i); }, [&](int i) { return 0.3 * std::pow(0.8, i); });
+        fail |= tridiag_case("graded", n, d, e);
+        fill([&](int i) { return std::pow(0.8, n - i); }, [&](int i) { return 0.3 * std::pow(0.8, n - i); });
+        fail |= tridiag_case("graded upwards", n, d, e);
+        fill([&](int i) { return 1.0 + (i % 3); }, [&](int) { return 1e-9 * urand(); });
+        fail |= tridiag_case("clustered", n, d, e);
+        fill([&](int) { return 1e30 * urand(); }, [&](int i) { return i % 5 == 4 ? 0.0 : 1e30 * urand(); });
+        fail |= tridiag_case("split", n, d, e);
+        fill([&](int i) { return std::fabs(n / 2 - i); }, [&](int) { return 1.0; });
+        fail |= tridiag_case("Wilkinson", n, d, e);
+        fill([&](int) { return 0.0; }, [&](int) { return 0.0; });
+        fail |= tridiag_case("zero", n, d, e);
+        fill([&](int) { return 0.0; }, [&](int) { return 1.0; });
+        fail |= tridiag_case("zero diagonal", n, d, e);
+        for (double bad : {std::nan(""), HUGE_VAL}) {
+            d[n / 2] = bad;
+            std::vector<double> dd = d, ee = e;
+            if (tridiag_qr(n, dd, ee, [](int, int, const std::vector<double>&) {})) fail = 1;
+        }
+    }
+    return fail;
+}
+
 int main() {
-    int fail = failing_allocations(40) | failing_allocations(64) | failing_allocations(300);
+    int fail = tridiagonal() | failing_allocations(40) | failing_allocations(64) | failing_allocations(300);
     for (int n : {1, 2, 3, 4, 7, 8, 15, 16, 31, 40}) {
         std::vector<double> a((size_t)n * n);
         for (int i = 0; i < n; ++i)

@@ -122,7 +122,18 @@ def test_the_gpu_cases_reach_the_shapes_they_name(rules):
     for cases, wfmt, want in ((G.WIDE_TILES, 0, WIDE), (G.BIG_TILES, 0, BIG), (G.MX_WIDE_TILES, W.WFMT_MXFP4, WIDE)):
         for s, T, R in cases:
             assert rules(T, s, R, wfmt)[0] == want, (s, T, R)
-    assert rules(96, G.WIDE, 3)[1] == 8
+    assert rules(96, G.WIDE, 3)[1] == rules(96, G.ROTATED, 4)[1] == rules(65, G.ROTATED, 4)[1] == 8
+
+    def deep_tiles(T, s, R):  # the launch's bound on its 64 x 64 up tiles; at most 256 take them
+        up = lambda n, per: -(-n // per)
+        slots = T * s.top_k
+        nt_e, nt_l = up(s.inter, 32), up(s.lore_rank, 64)
+        return (up(T, 64) * up(s.shared_inter, 32) + slots // 64 * max(nt_e, nt_l) + min(s.n_experts, R, slots) * nt_e +
+                min(s.n_experts, slots) * nt_l)
+
+    for T, R in ((130, 40), (203, 40)):
+        assert rules(T, G.SMALL_UP, R)[0] == SMALL and deep_tiles(T, G.SMALL_UP, R) > 256
+    assert deep_tiles(64, G.SMALL, 9) <= 256
     for s, T, fused in ((LIM.SMALL, 64, 1), (LIM.SMALL, 96, 1), (LIM.SMALL, 97, 0), (LIM.LONG, 64, 0), (LIM.NO_SHARED, 255, 1),
                         (LIM.NO_SHARED, 257, 0), (LIM.MX_GEMM, 97, 0)):
         assert rules(T, s, 7)[2] == fused, (s, T)

@@ -1,7 +1,9 @@
 """GPU parity of the grouped GEMM tiles where they can go wrong: contractions, rows, ranks and
-buckets that are no multiple of a tile, each of the tile shapes, the split of the shared
-block's down pass (and a workspace without room for it), gated and absent shared blocks, and
-the separate LoRE call.  Every token against the oracle."""
+buckets that are no multiple of a tile, each of the tile shapes (test_dispatch_cpu.py checks that
+the layers here reach them), the split of the shared block's down pass (and a workspace without
+room for it), k orders that start at other stages (rows of a multiple of 2 KiB), gated and absent
+shared blocks, and the separate LoRE call.  Every token against the oracle, but for the tall tiles
+every third."""
 import pytest
 import torch
 
@@ -20,6 +22,10 @@ SMALL = shape(200, 20, 5, 104, 168, 24)     # buckets of 16-32, k tails of 8 and
 WIDE = shape(264, 6, 3, 72, 2064, 136)      # buckets of 32-120; shared block split in 8
 BIG = shape(520, 4, 2, 136, 264, 40)        # buckets of 150
 NO_SHARED = shape(256, 8, 2, 128, 0, 16)
+SMALL_UP = shape(200, 64, 6, 168, 328, 24)  # too many tiles for 64 x 64: 128 x 64 in both passes
+# rows of 2 KiB (d) and 4 KiB (I_s): rotated k orders in the up pass, and in each of the 8 parts of the
+# shared down pass
+ROTATED = shape(1024, 8, 2, 256, 2048, 136)
 SPARSE = shape(520, 64, 3, 72, 104, 40)     # buckets of 6: LoRE alone stays on the streaming tiles
 
 
@@ -28,7 +34,8 @@ SPARSE = shape(520, 64, 3, 72, 104, 40)     # buckets of 6: LoRE alone stays on 
     (SMALL, 63, 9, False, True), (SMALL, 64, 9, False, True), (SMALL, 65, 20, True, True),
     (SMALL, 130, 3, False, False), (WIDE, 96, 3, True, True), (WIDE, 209, 2, False, True), (BIG, 300, 2, False, True),
     (BIG, 257, 4, True, True), (NO_SHARED, 129, 4, False, True), (NO_SHARED, 64, 1, False, False),
-    (SPARSE, 130, 20, False, False)])
+    (SPARSE, 130, 20, False, False), (SMALL_UP, 130, 40, False, True), (SMALL_UP, 203, 40, True, True),
+    (ROTATED, 96, 4, True, True), (ROTATED, 65, 4, False, False)])
 def test_gemm_edges(s, T, R, gate, fused, layer_call):
     say(f"gemm d={s.d} I={s.inter} Is={s.shared_inter} T={T} R={R} gate={gate} fused={fused}")
     c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=True, shared_gate=gate))
@@ -59,7 +66,7 @@ MX_WIDE = shape(384, 6, 3, 256, 1096, 40)   # buckets of 96 and more, few tiles
 
 
 @pytest.mark.parametrize("s,T,R", [(MX_SMALL, 71, 12), (MX_SMALL, 72, 5), (MX_SMALL, 97, 12), (MX_WIDE, 200, 3),
-                                   (MX_WIDE, 333, 6)] + MX_WIDE_TILES)
+                                   (MX_WIDE, 333, 6), (ROTATED, 97, 6)] + MX_WIDE_TILES)
 def test_gemm_mxfp4_edges(s, T, R):
     say(f"gemm mxfp4 d={s.d} I={s.inter} T={T} R={R}")
     c = Case(W.Workload("gemm", s, tokens=T, resident=R, skew=True, wfmt=W.WFMT_MXFP4))

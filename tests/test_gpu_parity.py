@@ -77,8 +77,8 @@ def test_ragged_layers(shape, T, R, layer_call):
         check_combine_in_layer_call(c)
 
 
-# A shape the prefill GEMMs never take (d not a multiple of 256), and one they take from
-# 256 tokens on.
+# Ragged and aligned layers around the slots and tokens that change the routing's launches; from 64
+# tokens on both run the GEMM tiles (test_gpu_layer_limits.py has the fused launches' own limits).
 LIMIT_STREAM = W.MoEShape(d=264, n_experts=16, top_k=8, inter=136, shared_inter=200, lore_rank=8,
                           dtype=W.DTYPE_BF16)
 LIMIT_GEMM = W.MoEShape(d=256, n_experts=16, top_k=4, inter=256, shared_inter=384, lore_rank=16,
@@ -86,16 +86,15 @@ LIMIT_GEMM = W.MoEShape(d=256, n_experts=16, top_k=4, inter=256, shared_inter=38
 
 
 @pytest.mark.parametrize("shape,T,R", [
-    (LIMIT_STREAM, 128, 6),   # T*K = 1024: the largest call of the three fused launches
-    (LIMIT_STREAM, 129, 6),   # 1032 slots: separate routing (decode kernel) and FFN launches
-    (LIMIT_GEMM, 255, 7),     # 1020 slots, below the GEMMs' 256 tokens: fused launches
-    (LIMIT_GEMM, 256, 7),     # 1024 slots, but the GEMMs apply: decode routing, then the GEMMs
-    (LIMIT_GEMM, 257, 7),     # past the decode routing's 256 tokens: prefill routing and GEMMs
-], ids=["stream-1024", "stream-1032", "gemm-T255", "gemm-T256", "gemm-T257"])
+    (LIMIT_STREAM, 128, 6),   # 1024 slots, routing with a row per wave
+    (LIMIT_STREAM, 129, 6),   # 1032 slots
+    (LIMIT_GEMM, 255, 7),     # 1020 slots, one routing launch (tiles, since x goes to the host)
+    (LIMIT_GEMM, 256, 7),     # 1024 slots, the last one-launch routing
+    (LIMIT_GEMM, 257, 7),     # three routing launches
+], ids=["ragged-1024", "ragged-1032", "T255", "T256", "T257"])
 def test_layer_call_at_its_dispatch_limits(shape, T, R):
-    """moe_layer_gpu on either side of each limit that picks its launches (slots of the fused
-    launches, tokens of the decode routing, tokens of the prefill GEMMs): every token's
-    routing and outputs against the oracle."""
+    """moe_layer_gpu around 1024 slots and around the one-launch routing's 256 tokens: every
+    token's routing and outputs against the oracle."""
     say(f"layer-call limits d={shape.d} K={shape.top_k} T={T} R={R}")
     c = Case(small_wl(shape, T, R))
     c.run_gpu(layer_call=True)
@@ -280,9 +279,9 @@ def test_host_copies_match_device_outputs(shape, T, R, layer_call):
     assert np.array_equal(to_np(run.x_host[:T]), c.x)
 
 
-# Decode routing of more slots than its bucketing block keeps in LDS (T*K = 2560 > 1024
-# at T = 256, the largest decode batch): that block reads the keys the top-K blocks
-# published twice, once per pass.
+# One-launch routing of more slots than its bucketing block keeps in LDS (T*K = 2560 at T = 256;
+# 2048 with the tiles that run here, 1024 with a row per wave): that block reads the keys the
+# top-K blocks published twice, once per pass.
 MANY_SLOTS = W.MoEShape(d=200, n_experts=20, top_k=10, inter=104, shared_inter=168, lore_rank=24,
                         dtype=W.DTYPE_BF16)
 

@@ -1,5 +1,5 @@
-"""GPU parity of the prefill path: at T >= 256 tokens (bf16, tile-aligned sizes) the
-HIT experts and the shared block run as grouped MFMA GEMMs.
+"""GPU parity of the prefill path: with many tokens (bf16 activations) the HIT experts, the
+shared block and the LoRE corrections run as grouped MFMA GEMMs.
 
   - a reduced layer (d=256, N=16, K=4, I=256, I_s=384, r=16) at T=300 and 600, every
     token against the oracle, all resident and partly resident (LoRE + exact misses),

@@ -73,6 +73,12 @@ CASES = [
     (MoEShape(256, 24, 6, 128, 0, 16, BF16), 33, 5, 1, 0.36),   # no shared block
     (MoEShape(2048, 64, 6, 1408, 2816, 32, BF16), 32, 4, 2, 0.0),  # DSV2-Lite shapes
     (MoEShape(2048, 64, 6, 1408, 2816, 32, BF16), 32, 4, 1, 0.33),
+    # 64 tokens and more on the GEMM tiles: 64 x 64 up tiles, the shared block split in 8, no pool at all
+    (MoEShape(1024, 24, 6, 64, 2048, 16, BF16), 64, 3, 1, 0.0),
+    (MoEShape(1024, 24, 6, 64, 2048, 16, BF16), 97, 3, 1, 0.34),
+    # more predictions than the update keeps in flight at a time
+    (MoEShape(264, 24, 10, 64, 96, 16, BF16), 70, 3, 1, 0.5),
+    (MoEShape(264, 24, 17, 64, 96, 16, BF16), 21, 3, 1, 0.0),
 ]
 
 

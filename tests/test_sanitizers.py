@@ -4,7 +4,8 @@
   - the library's host C++ (cache, exact CPU residual, LoRE fit, speculative prefetch,
     split planner and the C ABI's validation; tests/sanitize/host_driver.cpp), with the GPU
     launchers replaced by stubs that report no device;
-  - the LoRE fit's host linear algebra (Jacobi eigensolver, Cholesky; lore_math_driver.cpp);
+  - the LoRE fit's host linear algebra (Jacobi eigensolver, QR iteration, Cholesky), and the
+    fit with each of its allocations failing in turn (lore_math_driver.cpp);
   - a host model of the expert-FFN tile indexing (tile_driver.cpp): every tile of the
     grouped-FFN and decode-layer launches replays its operand loads and output stores,
     through the same index helpers as the kernels (csrc/tile_index.h), on host buffers of

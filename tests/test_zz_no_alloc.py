@@ -1,7 +1,8 @@
 """The no-allocation layer call (moe_layer_gpu_noalloc, workspace in a static device array)
 against the layer call with a caller's workspace (moe_layer_gpu): the same outputs, on two
-calls in a row, the second with fewer tokens, on a DeepSeek-V2-Lite-shaped layer and a
-ragged fp32 layer."""
+calls in a row, the second with fewer tokens, on a DeepSeek-V2-Lite-shaped layer (decode, and a
+prefill whose split of the shared block the static workspace has no room for) and a ragged
+fp32 layer."""
 import numpy as np
 import pytest
 import torch
@@ -31,9 +32,12 @@ def _outputs(run, T):
 
 
 @pytest.mark.parametrize("wl,Ts", [(W.WORKLOADS["dsv2_decode_t32"], (32, 8)),
+                                   (W.WORKLOADS["dsv2_decode_t32"], (1000, 96)),
                                    (W.Workload("ragged_f32", RAGGED_F32, tokens=41, resident=4, skew=False), (41, 6))])
 def test_noalloc_layer_call_matches_workspace_call(wl, Ts):
     s = wl.shape
+    if max(Ts) == 1000:
+        assert spice.spice_workspace_bytes(spice.make_cfg(s, wl.resident), 1000) > spice.SPICE_NOALLOC_SCRATCH_BYTES
     host = LY.HostLayer(wl, 0)
     dev = LY.DeviceLayer(host, host_exact=False)
     ref_run = LY.LayerRun(s, max(Ts), dev.C, tau=wl.tau)
