@@ -169,6 +169,12 @@ WsLayout ws_layout(const spice_moe_cfg_t& c, int32_t T) {
     L.u = off;      off += align256(slots * (size_t)c.lore_rank * sizeof(float));
     L.sgate = off;  off += align256(t * sizeof(float));
     L.base = off;
+    L.zpart = off;
+    if (T >= kRouteTiledMinT) {
+        const size_t groups = (t + kRouteTileTok - 1) / kRouteTileTok;
+        const int zp = route_parts(T, c.n_experts, c.d, c.dtype, SIZE_MAX);
+        if (zp > 1) off += align256((size_t)zp * groups * kRouteTileTok * c.n_experts * sizeof(double));
+    }
     const int parts = c.dtype == SPICE_BF16 ? gemm_shared_parts(T, c.d, c.n_experts, c.top_k, c.n_slots, c.inter,
                                                                 c.shared_inter) : 1;
     L.part = off;   off += parts > 1 ? align256((size_t)parts * t * c.d * sizeof(float)) : 0;
@@ -244,7 +250,7 @@ spice_status_t prep_route(const spice_moe_cfg_t* cfg, int32_t T, const void* x, 
     a.norm_topk = c.norm_topk; a.conf_mode = c.conf_mode; a.tau = c.tau;
     a.x = x; a.wg = w_gate; a.bias = logit_bias; a.resident_slot = resident_slot; a.conf = conf;
     a.logits_out = logits; a.logits_ws = reinterpret_cast<double*>(wsb + L.logits);
-    a.part_ws = reinterpret_cast<double*>(wsb + L.h); a.part_bytes = L.base - L.h;
+    a.part_ws = reinterpret_cast<double*>(wsb + L.zpart); a.part_bytes = ws_bytes >= L.part ? L.part - L.zpart : 0;
     a.topk_idx = topk_idx; a.topk_w = topk_w; a.slot_class = slot_class;
     a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
     a.ctrl = reinterpret_cast<uint32_t*>(wsb);
@@ -327,7 +333,7 @@ spice_status_t prep_ffn(const spice_moe_cfg_t* cfg, int32_t T, const void* x, co
     a.w13_pool = w13_pool; a.w2_pool = w2_pool; a.w13s = w13_shared; a.w2s = w2_shared;
     a.lore_A = lore_A; a.lore_B = lore_B; a.y_slots = y_slots; a.y_shared = y_shared;
     a.h = wsb + L.h; a.hs = wsb + L.hs; a.u = reinterpret_cast<float*>(wsb + L.u);
-    a.part = L.total > L.base && ws_bytes >= L.total ? reinterpret_cast<float*>(wsb + L.part) : nullptr;
+    a.part = L.total > L.part && ws_bytes >= L.total ? reinterpret_cast<float*>(wsb + L.part) : nullptr;
     a.ctrl = reinterpret_cast<uint32_t*>(wsb);
     a.wfmt = c.wfmt;
     return SPICE_OK;

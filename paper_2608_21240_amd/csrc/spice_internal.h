@@ -75,8 +75,9 @@ struct WsLayout {
     size_t hs;      // shared-block intermediate [T][I_s + kHPad] (dtype)
     size_t u;       // LoRE A x, fp32 [T*K][r]
     size_t sgate;   // output gate of the shared block, fp32 [T]
-    size_t base;    // bytes every call needs
-    size_t part;    // the shared block's partial results, fp32 [parts][T][d] (used when the workspace has them)
+    size_t base;    // bytes every call needs; the rest is used when the workspace has it
+    size_t zpart;   // partial logits of the tiled routing, fp64 (its own: no FFN buffer is touched by a routing call)
+    size_t part;    // the shared block's partial results, fp32 [parts][T][d]
     size_t total;
 };
 WsLayout ws_layout(const spice_moe_cfg_t& c, int32_t T);
@@ -94,7 +95,7 @@ struct RouteArgs {
     const float* conf;
     double* logits_out;   // caller's, nullable
     double* logits_ws;    // workspace copy read by the top-K step
-    double* part_ws;      // workspace the FFN uses later: partial logits of the tiled routing
+    double* part_ws;      // partial logits of the tiled routing
     size_t part_bytes;    // its size
     int32_t* topk_idx;
     float* topk_w;

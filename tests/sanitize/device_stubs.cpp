@@ -6,9 +6,17 @@
 namespace spice {
 bool expert_gemm_applies(const FfnArgs&) { return false; }
 hipError_t launch_expert_gemm(const FfnArgs&, bool, bool, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_route_bucket(const RouteArgs&, hipStream_t) { return hipErrorNoDevice; }
+RouteArgs last_route{};  // what the last call would have launched
+FfnArgs last_ffn{};
+hipError_t launch_route_bucket(const RouteArgs& a, hipStream_t) {
+    last_route = a;
+    return hipErrorNoDevice;
+}
 hipError_t launch_layer_decode(const RouteArgs&, const FfnArgs&, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_expert_ffn(const FfnArgs&, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_expert_ffn(const FfnArgs& a, hipStream_t) {
+    last_ffn = a;
+    return hipErrorNoDevice;
+}
 hipError_t launch_expert_ffn_mx(const FfnArgs&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_shared_gate(const void*, const void*, int32_t, int32_t, int32_t, float*, hipStream_t) {
     return hipErrorNoDevice;

@@ -17,7 +17,13 @@
 #include <cstring>
 #include <vector>
 
+#include "spice_internal.h"
 #include "spice_moe.h"
+
+namespace spice {
+extern RouteArgs last_route;  // device_stubs.cpp
+extern FfnArgs last_ffn;
+}  // namespace spice
 
 static int g_fail = 0;
 #define CHECK(c)                                                              \
@@ -64,6 +70,53 @@ static spice_moe_cfg_t cfg_of(int d, int N, int K, int I, int Is, int r, int C, 
     c.d = d; c.n_experts = N; c.top_k = K; c.inter = I; c.shared_inter = Is; c.lore_rank = r; c.n_slots = C;
     c.dtype = dtype; c.norm_topk = 0; c.conf_mode = SPICE_CONF_INPUT; c.tau = 0.5f; c.wfmt = wfmt;
     return c;
+}
+
+// The buffers that a routing call and an FFN call take from one workspace: inside it, and apart but
+// for the control region (so that the two may run at the same time).
+static void workspace_buffers() {
+    const int shapes[][7] = {{64, 8, 2, 32, 48, 8, 4}, {2048, 64, 6, 1408, 2816, 32, 32}, {1024, 256, 8, 64, 0, 0, 0}};
+    for (const auto& f : shapes)
+        for (int dtype : {SPICE_BF16, SPICE_F32})
+            for (int T : {1, 100, 207, 208, 256, 257, 1000, 4096}) {
+                const spice_moe_cfg_t c = cfg_of(f[0], f[1], f[2], f[3], f[4], f[5], f[6], dtype);
+                const size_t bytes = spice_workspace_bytes(&c, T);
+                char* ws = reinterpret_cast<char*>(0x10000000000);  // never dereferenced
+                char* const x = reinterpret_cast<char*>(0x1000);
+                char* const y = reinterpret_cast<char*>(0x20000000000);
+                float* yf = reinterpret_cast<float*>(y);
+                int32_t* pi = reinterpret_cast<int32_t*>(x);
+                float* pf = reinterpret_cast<float*>(x);
+                for (size_t less : {(size_t)0, (size_t)256}) {
+                    CHECK(moe_route_bucket(&c, T, x, x, nullptr, pi, pf, nullptr, pi, pf, reinterpret_cast<uint8_t*>(x), pi,
+                                           pi, pi, nullptr, ws, bytes - less, nullptr) != SPICE_OK);
+                    CHECK(moe_expert_ffn_grouped(&c, T, x, pi, pi, pi, x, x, x, x, x, x, yf, yf + ((size_t)1 << 32), ws,
+                                                 bytes - less, nullptr) != SPICE_OK);
+                    if (less) continue;
+                    const spice::RouteArgs& r = spice::last_route;
+                    const spice::FfnArgs& a = spice::last_ffn;
+                    const size_t es = dtype == SPICE_BF16 ? 2 : 4, t = (size_t)T, slots = t * c.top_k;
+                    const int parts = dtype == SPICE_BF16 ? spice::gemm_shared_parts(T, c.d, c.n_experts, c.top_k, c.n_slots,
+                                                                                    c.inter, c.shared_inter) : 1;
+                    struct Range { const void* p; size_t n; };
+                    const Range route[] = {{r.logits_ws, t * c.n_experts * 8}, {r.part_ws, r.part_bytes}};
+                    const Range ffn[] = {{a.h, slots * (c.inter + spice::kHPad) * es}, {a.hs, t * (c.shared_inter + spice::kHPad) * es},
+                                         {a.u, slots * c.lore_rank * 4}, {a.part, a.part ? parts * t * c.d * 4 : 0}};
+                    auto inside = [&](const Range& q) {
+                        return !q.n || (q.p >= ws + SPICE_WS_CONTROL_BYTES && (const char*)q.p + q.n <= ws + bytes);
+                    };
+                    for (const Range& q : route) {
+                        CHECK(inside(q));
+                        for (const Range& o : ffn)
+                            CHECK(!q.n || !o.n || (const char*)q.p + q.n <= o.p || (const char*)o.p + o.n <= q.p);
+                    }
+                    for (const Range& o : ffn) CHECK(inside(o));
+                    if (T >= 208) {  // room for every part the call would take
+                        const int p = spice::route_parts(T, c.n_experts, c.d, c.dtype, SIZE_MAX);
+                        CHECK(spice::route_parts(T, c.n_experts, c.d, c.dtype, r.part_bytes) == p);
+                    }
+                }
+            }
 }
 
 static void validation() {
@@ -323,6 +376,7 @@ static void cache_bookkeeping() {
 }
 
 int main() {
+    workspace_buffers();
     validation();
     //             d    N   K  I   T   dtype       wfmt
     exact_residual(40, 6, 2, 24, 7, SPICE_F32, SPICE_WFMT_DTYPE);
