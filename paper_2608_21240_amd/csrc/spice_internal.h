@@ -27,14 +27,14 @@ constexpr int kRouteTokenMaxT = 256;
 constexpr int kRouteTiledMinT = 208;
 // Contraction parts per group of 16 tokens of the tiled logits: as many as fill the 256 CUs with a
 // block each (a group's logits are bound by its CU's fp64 matrix rate), at least two passes of
-// 128 bytes per part, and partial logits that fit part_bytes.  One for small products, whose logits
-// take less time than a group's wait for its parts (whole / split: N = 12, d = 144 15.2 / 16.6 us,
-// N = 64, d = 256 22.4 / 24.6; N = 5, d = 3736 23.1 / 17.4, N = 35, d = 1440 26.4 / 21.2).
+// 128 bytes per part, and partial logits that fit part_bytes.  One for small products and short rows,
+// whose logits take less time than a group's wait for its parts (whole / split: N = 12, d = 144
+// 15.2 / 16.6 us, N = 64, d = 256 22.4 / 24.6, N = 128, d = 256 31.1 / 33.0; N = 5, d = 3736 23.1 / 17.4, N = 35, d = 1440 26.4 / 21.2).
 constexpr int kRouteTileTok = 16, kRouteMaxParts = 8;
 inline int route_parts(int32_t T, int32_t N, int32_t d, int32_t dtype, size_t part_bytes) {
-    if ((int64_t)N * d < (d <= 1024 ? 24000 : 12000)) return 1;
     const int groups = (T + kRouteTileTok - 1) / kRouteTileTok;
     const int npass = d * (dtype == SPICE_BF16 ? 2 : 4) / 128;
+    if (npass < 8 || (int64_t)N * d < (d <= 1024 ? 24000 : 12000)) return 1;
     const size_t per_part = (size_t)groups * kRouteTileTok * N * sizeof(double);
     int p = kRouteMaxParts;
     p = p < 256 / groups ? p : 256 / groups;
