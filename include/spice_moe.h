@@ -49,7 +49,7 @@ typedef enum {
     SPICE_ERR_INVALID = -1,     /* a bad argument (NULL, out of range, overflow, aliasing) */
     SPICE_ERR_UNSUPPORTED = -2, /* valid but not handled: size alignment, dtype, N > 256 ... */
     SPICE_ERR_HIP = -3,         /* the HIP runtime reported an error (launch, copy, earlier fault) */
-    SPICE_ERR_WORKSPACE = -4,   /* workspace smaller than spice_workspace_bytes() */
+    SPICE_ERR_WORKSPACE = -4,   /* workspace smaller than the call needs (see spice_workspace_bytes) */
     SPICE_ERR_INTERNAL = -5
 } spice_status_t;
 
@@ -111,8 +111,12 @@ enum { SPICE_WFMT_DTYPE = 0, SPICE_WFMT_MXFP4 = 2 };
 /* Size alignment required: d, inter and shared_inter multiples of 8 (bf16) or 4 (fp32);
  * lore_rank a multiple of 8 (bf16) or 4 (fp32). */
 
-/* Bytes of device workspace that a call with T tokens needs (every entry point below
- * accepts the same workspace).  Returns 0 for an invalid cfg or T. */
+/* Bytes of device workspace for a call with T tokens (every entry point below accepts the same
+ * workspace).  Returns 0 for an invalid cfg or T.
+ * The end of it is optional, a call without it only takes longer: the partial results of split
+ * contractions, of the routing's logits (at most 32 KiB x N) and, behind them, of the shared block's
+ * down projection (at most 8 x T x d fp32; without them y_shared differs by the order of its fp32
+ * sums).  A SPICE_ERR_WORKSPACE message names the smallest size that the call accepts. */
 size_t spice_workspace_bytes(const spice_moe_cfg_t* cfg, int32_t T);
 
 /* Zero the control region of a device workspace (a fill kernel on `stream`). */
@@ -168,8 +172,8 @@ spice_status_t spice_wait_ready(const volatile uint32_t* ready, uint32_t value, 
  *   host_out      host copies for the CPU path (see spice_host_out_t), or NULL
  * The workspace also receives the device work lists of the buckets (per class, the
  * non-empty buckets in ascending expert order with start and size), which the fused
- * layer path reads.  Up to 256 tokens the call is one launch; from 208 on the logits are
- * computed as fp64 MFMA tiles.
+ * layer path reads.  Up to 256 tokens the call is one launch.  Some calls of 208 tokens or more
+ * and all of 257 or more compute the logits as fp64 MFMA tiles (another order of the same fp64 sums).
  */
 spice_status_t moe_route_bucket(const spice_moe_cfg_t* cfg, int32_t T, const void* x,
                                 const void* w_gate, const float* logit_bias,
@@ -183,7 +187,8 @@ spice_status_t moe_route_bucket(const spice_moe_cfg_t* cfg, int32_t T, const voi
  * Step 3: grouped SwiGLU FFN y = W2 (silu(W1 x) * (W3 x)) (Eq. 6) for every HIT slot,
  * grouped by expert, plus the shared block S(x) (Sec. 2.1, 4.2) for all T tokens.
  * When lore_A and lore_B are both non-NULL the LoRE corrections of step 4 are computed
- * in the same launches (the same result as calling lore_surrogate_apply).
+ * in the same launches: what lore_surrogate_apply computes, up to the order of its fp32 sums
+ * (with many tokens the two may take different tiles).
  *   x, perm, offsets       as produced/consumed by moe_route_bucket
  *   resident_slot device [N] int32, as in moe_route_bucket
  *   w13_pool      device [C][2I][d]  rows 0..I-1 gate W1, rows I..2I-1 up W3 (dtype)
@@ -256,12 +261,13 @@ spice_status_t moe_combine(const spice_moe_cfg_t* cfg, int32_t T, const float* t
  * shared block with the LoRE corrections fused (as moe_expert_ffn_grouped, or
  * moe_expert_ffn_grouped_gated when w_shared_gate != NULL), then, if out != NULL, the
  * combine with `resid` (as moe_combine).  Every output is the one those calls define.
- * The work that does not depend on routing is not ordered after it (Sec. 4.2: the shared
- * block S is always resident): for T <= 256 and T*K <= 1024 (routed experts in the cfg
+ * The work that does not depend on routing is not ordered after it (Sec. 4.2: the
+ * shared block S is always resident): for T <= 256 and T*K <= 1024 (routed experts in the cfg
  * dtype or in MXFP4; bf16 activations only while the prefill GEMMs, which take calls of many
- * tokens, do not apply or would take longer, as in small layers) the call is three launches in which routing runs beside the shared block's up projection, the
- * shared block's down projection beside the routed up projections, and each routed tile
- * finds its bucket from the routing itself; otherwise the separate launches of those calls.
+ * tokens, do not apply or would take longer, as in small layers) the call is three launches in
+ * which routing runs beside the shared block's up projection, the shared block's down projection
+ * beside the routed up projections, and each routed tile finds its bucket from the routing
+ * itself; otherwise the separate launches of those calls.
  * For the CPU path of Sec. 4.3, pass host_out (its ready word is stored as soon as the
  * copies have landed, before the FFN ends) and out = NULL, run moe_exact_residual_host on
  * the copies, then moe_combine.
@@ -282,12 +288,13 @@ spice_status_t moe_layer_gpu(const spice_moe_cfg_t* cfg, int32_t T, const void* 
 
 /*
  * moe_layer_gpu for callers that cannot allocate device memory: code under HIP graph
- * capture, tight serving loops, and harnesses that forbid hipMalloc.  The same launches and
- * outputs as moe_layer_gpu; instead of a caller's workspace it uses a static device array
- * of SPICE_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on until the
+ * capture, tight serving loops, and harnesses that forbid hipMalloc.  The launches and outputs
+ * of moe_layer_gpu on a workspace of SPICE_NOALLOC_SCRATCH_BYTES, which for some prefills has no
+ * room for the optional end of spice_workspace_bytes; instead of a caller's workspace it uses
+ * a static device array of that size that the library holds on each GPU it runs on until the
  * process ends (zero when loaded; its device address is looked up once per device).  The
  * call allocates nothing.  The caller still passes every input and output.
- *   Errors: those of moe_layer_gpu; UNSUPPORTED when spice_workspace_bytes(cfg, T) exceeds
+ *   Errors: those of moe_layer_gpu; UNSUPPORTED when the smallest workspace of the call exceeds
  *   SPICE_NOALLOC_SCRATCH_BYTES.  Device flags raised by the kernels are not reported.
  * Every call on one GPU shares that GPU's array: calls that overlap on one GPU (different
  * streams, or host threads without ordering) race and must not be issued.
@@ -461,7 +468,8 @@ spice_status_t moe_expert_ffn_fetched(const spice_moe_cfg_t* cfg, int32_t T, con
 /*
  * Speculative prefetching (Sec. 4.1, Eq. 2-5, Alg. 1).  A draft rollout starts from the
  * current layer's input hidden state h0 [T][d] and runs depth delta = 1, 2, ... with the
- * weights of layer l + delta.  Each depth is three calls on one stream:
+ * weights of layer l + delta.  Each depth is three calls on one stream (or two: moe_layer_gpu
+ * with out NULL does the first two):
  *   1. moe_route_bucket on the draft state with the future layer's router, every expert
  *      absent (resident_slot all -1), conf all 0, cfg->conf_mode SPICE_CONF_INPUT,
  *      cfg->norm_topk 0 and cfg->tau > 0: every slot is then LoRE and topk_w holds the
@@ -552,8 +560,9 @@ spice_status_t moe_cache_prefetch(spice_cache_t* cache, int32_t layer, int32_t s
  * (minimum-norm A); the loss is the sum of the squared singular values beyond the r-th,
  * and r >= n fits exactly (directions beyond n are zero rows of A / columns of B).
  * E_e and S run on the GPU (the grouped-FFN kernels), the n x n Gram matrices in fp64 on
- * the GPU, their eigen-decomposition and solve in fp64 on the host.  The call is
- * synchronous: it returns when A and B are written.
+ * the GPU; their eigen-decomposition and solve run in fp64 on the GPU for more than 48 tokens
+ * (the host iterates on the tridiagonal form), on the host for fewer.  The call is synchronous:
+ * it returns when A and B are written.
  *   n            calibration tokens, 1 <= n <= min(d, 1024)
  *   r            rank, 1 <= r <= d (the LoRE rank; it may differ from cfg->lore_rank)
  *   x            device [n][d] (dtype) calibration hidden states, linearly independent
@@ -562,7 +571,9 @@ spice_status_t moe_cache_prefetch(spice_cache_t* cache, int32_t layer, int32_t s
  *   A_out, B_out device fp32 [r][d] and [d][r] out
  *   y_out        nullable device fp32 [n][d] out: the residual targets E_e(x) - S(x)
  *   loss_out     nullable host out: Eq. 10's minimum (fp64, from the residual spectrum)
- *   ws, ws_bytes workspace of spice_lore_fit_workspace_bytes(cfg, n, r) bytes
+ *   ws, ws_bytes workspace of spice_lore_fit_workspace_bytes(cfg, n, r) bytes.  For more than 48
+ *                tokens its end holds the GPU's eigenvectors, factor and rotations; without it the
+ *                call runs the n x n work on the host, many times as long (n = 512: 0.9 s, not 14 ms)
  * Returns UNSUPPORTED for n > min(d, 1024), INVALID for linearly dependent tokens.
  */
 size_t spice_lore_fit_workspace_bytes(const spice_moe_cfg_t* cfg, int32_t n, int32_t r);

@@ -25,21 +25,22 @@
 // frees the buffer just read for the stage S ahead.
 // MXFP4 HIT experts: the codes are staged as they are (a quarter of the bytes) and decoded
 // after the read from LDS, once per wave and tile instead of once per 16 tokens as in the
-// streaming tiles: DeepSeek-V2-Lite sizes, all resident, T = 777 694 -> 261 us per call; Qwen2
-// sizes T = 1000 5577 -> 1206.
+// streaming tiles: DeepSeek-V2-Lite sizes, all resident, T = 777 693 -> 229 us per call; Qwen2
+// sizes T = 1000 5609 -> 1116.
 // What bounds it: with short buckets, the weight stream from HBM (bytes in flight: S - 1 stages
-// per block), with long ones the MFMAs (960 - 1020 TFLOP/s at Qwen2 sizes, T = 4096).  Against
+// per block), with long ones the MFMAs (1030 TFLOP/s at Qwen2 sizes, T = 4096).  Against
 // one 256 x 256 two-stage shape for every T, with 32 or more tokens per pass of the streaming
-// tiles below T = 256 and separate LoRE launches (us per layer call, DeepSeek-V2-Lite sizes):
-// T = 64 204 -> 187, T = 192 259 -> 209, T = 300 311 -> 189, T = 1000 357 -> 263, T = 4096 of
-// Qwen2 3661 -> 3581; Qwen2 T = 96 882 -> 604, T = 300 1325 -> 884 (its shared block split).
+// tiles below T = 256 and separate LoRE launches (us per layer call): DeepSeek-V2-Lite sizes
+// with 48 experts resident T = 64 202 -> 185, T = 192 261 -> 207, T = 300 347 -> 220, with 32
+// T = 1000 360 -> 245, T = 2000 514 -> 368; Qwen2 sizes, all resident, skewed, T = 96 1062 -> 707,
+// T = 300 1310 -> 911 (its shared block split), T = 1000 1700 -> 1429, T = 4096 3743 -> 3490.
 // Tiles: the shared block first, then the HIT experts in id order, then the LORE buckets.  In the
-// bf16 shapes with one block per CU (Wide, Big) the reverse: a LORE tile lasts as long as any
+// bf16 shapes with one block per CU (Deep, Wide, Big) the reverse: a LORE tile lasts as long as any
 // other (its loads' latency, 27 - 36 us at d = 2048) and was the launch's tail on a fifth of the
 // CUs, and the shared tiles, which L2 feeds, fill the CUs that the last HIT tiles leave
-// (T = 1000 of DeepSeek-V2-Lite 257 -> 242 us a call, T = 2000 367 -> 362, Qwen2 T = 4096 3485 ->
-// 3460).  With two blocks per CU, or MXFP4 tiles, whose weights stream at a lower rate, the shared
-// block first is the better (T = 300 171 / 176, MXFP4 T = 777 229 / 239).
+// (T = 1000 of DeepSeek-V2-Lite 6 % of the call, T = 2000 and Qwen2's T = 4096 1 %).  With two blocks
+// per CU, or MXFP4 tiles, whose weights stream at a lower rate, the shared block first is the
+// better (3 % at T = 300, MXFP4 4 % at T = 777).  Deep launches have a CU for every tile.
 // Inside a group the token tiles of one weight tile are consecutive (the weight tile is then
 // served from L2), and consecutive tiles are kept on one XCD.
 #include <hip/hip_runtime.h>
@@ -52,14 +53,14 @@
 namespace spice {
 namespace {
 
-// Deep is Small's rows halved with eight stages in flight, for up launches whose tiles do not
-// fill the GPU (a draft rollout's shared block and LoRE factors): there a tile waits for its own
-// loads, not for the memory's rate (T = 64: 18.6 -> 14.0 us).
 // Tile shapes: BM weight rows x BT tokens, a grid of WF x WT waves, S stages in LDS, W waves
 // per SIMD the register budget targets, L waves that issue the stages' loads.  Of the big tiles'
 // eight waves four load, one per SIMD, so the others' MFMAs never wait behind the load queue
-// (Qwen2, T = 4096, Big: 3764 -> 3633 us; T = 1000 of DeepSeek-V2-Lite, Wide: 244 -> 241).  Measured beside them and slower over their ranges:
-// 128 x 128 (2 or 4 stages), 64 x 64, 128 x 32 and 256 x 64 tiles.
+// (Qwen2, T = 4096, Big: 3.5 %; T = 1000 of DeepSeek-V2-Lite, Wide: 1 %).  Deep is Small's rows halved
+// with eight stages in flight, for up launches of at most a tile per CU (a draft rollout's shared
+// block and LoRE factors): there a tile waits for its own loads, not for the memory's rate (T = 64:
+// 18.6 -> 14.0 us).  Measured beside them and slower over their ranges: 128 x 128 (2 or 4 stages),
+// 64 x 64 with three stages, 128 x 32 and 256 x 64 tiles.
 template <int BM_, int BT_, int WF_, int WT_, int S_, int W_, int L_>
 struct Shape {
     static constexpr int BM = BM_, BT = BT_, WF = WF_, WT = WT_, S = S_, W = W_;
@@ -94,8 +95,8 @@ using Big = Shape<256, 256, 2, 4, 2, 2, 4>;
 using Wide = Shape<256, 128, 4, 2, 3, 2, 4>;
 using Small = Shape<128, 64, 2, 2, 3, 2, 4>;
 using Deep = Shape<64, 64, 2, 2, 8, 2, 4>;
-static_assert(Big::BM == kGemmBigTile[0] && Big::BT == kGemmBigTile[1] && Wide::BM == kGemmWideTile[0] && Wide::BT == kGemmWideTile[1] && Small::BM == kGemmSmallTile[0] &&
-                  Small::BT == kGemmSmallTile[1],
+static_assert(Big::BM == kGemmBigTile[0] && Big::BT == kGemmBigTile[1] && Wide::BM == kGemmWideTile[0] &&
+                  Wide::BT == kGemmWideTile[1] && Small::BM == kGemmSmallTile[0] && Small::BT == kGemmSmallTile[1],
               "the shapes' tiles as the split rule knows them");
 
 constexpr int kBK = 64;                          // contraction per stage
@@ -373,7 +374,7 @@ __device__ __forceinline__ void product(unsigned char* s_lds, int nk, uint32_t f
 // and the token operand reads the same k (chunk 4 quad + u of its 256-byte row).  load(buf, kt, l)
 // issues the l-th load of a stage: a wave's own loads go out between its MFMAs, not in one run
 // before its fragment reads, where the MFMAs waited for the load queue (T = 777 of
-// DeepSeek-V2-Lite: 242 -> 229 us a call; the bf16 loop, whose stages hold four times the
+// DeepSeek-V2-Lite: 5 % of the call; the bf16 loop, whose stages hold four times the
 // weight bytes, gains nothing from it).  Reading half a stage ahead, as product() does, gave
 // nothing here.
 template <class C, bool kUp, int NL, class Load>

@@ -138,8 +138,8 @@ __device__ __forceinline__ double block_sum(double v, double* part) {
 //   V[k][k+1 .. n)  reflector k (its first entry 1), tau[k] its factor: H = I - tau v v^T
 //   p[k & 1][i]     (A v)[i], read by the next launch
 //   dv[k], ev[k]    diagonal and subdiagonal of the tridiagonal form
-// Bound by the launch and two dependent round trips to L2 per step (5.5 us a step at n = 512;
-// the matrix, 2 MB, stays in L2): 2.8 ms of the fit, whose Jacobi rotations on one host core
+// Bound by the launch and two dependent round trips to L2 per step (6 us a step at n = 512;
+// the matrix, 2 MB, stays in L2): 3.1 ms of the fit, whose Jacobi rotations on one host core
 // took 0.9 s (the whole fit of n = 512 tokens: 928 -> 14.1 ms).
 __global__ __launch_bounds__(kEigThreads) void fit_tridiag_kernel(int n, int k, double* A, double* V, double* tau, double* p,
                                                                   double* dv, double* ev) {
@@ -215,8 +215,8 @@ __global__ __launch_bounds__(kEigThreads) void fit_tridiag_kernel(int n, int k, 
 // chain over k stays in a register.  A block owns kRotCols components of every vector in LDS,
 // one per lane, so no block meets another.  A sweep's rotations are loaded into registers while
 // the sweep before it runs and staged in LDS, and a batch's operands are read from LDS while
-// the one before it is rotated: read straight from L2 the chain waited 73 ns per rotation, now
-// 28 ns (303k rotations at n = 512).
+// the one before it is rotated; read straight from L2 the chain took more than twice as long.
+// 30 ns a rotation (263k at n = 512, 7.8 ms of the fit).
 constexpr int kRotCols = 16, kRotBatch = 8;
 // A batch read ahead reaches up to 3 kRotBatch entries past a sweep: of the rotations, their
 // padding; of a vector's rows (kRotCols doubles each), the rotations behind them and the padding.

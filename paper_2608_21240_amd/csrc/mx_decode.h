@@ -14,8 +14,6 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // 2^-127 for s = 0, NaN for s = 255; the conversion applies it exactly.
 // Bit 22 marks both special cases; without a compare, which the compiler turned into branches
 // between the loads and the MFMAs.
-// Bit 22 marks both special cases; without a compare, which the compiler turned into branches
-// between the loads and the MFMAs.
 __device__ __forceinline__ float e8m0(uint32_t s) {
     const uint32_t special = (((s + 1u) & 0xFEu) - 1u) >> 31;  // s is 0 or 255
     return __uint_as_float((s << 23) | (special << 22));
