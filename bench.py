@@ -54,12 +54,13 @@ TRAFFIC_RECORDS = {
                            "paper_2608_21240_amd/csrc/route_device.h",
                            "paper_2608_21240_amd/csrc/expert_ffn_tiles.h",
                            "paper_2608_21240_amd/csrc/expert_ffn_mx_tiles.h",
+                           "paper_2608_21240_amd/csrc/mx_decode.h",
                            "paper_2608_21240_amd/csrc/tile_index.h",
                            "paper_2608_21240_amd/csrc/combine.hip",
                            "paper_2608_21240_amd/csrc/spice_internal.h"),
-        "source_sha256_16": "85a4b3319e438b10",
-        "fetch_kib_per_call": 12031.4 + 184134.4 + 90267.5 + 905.7,
-        "write_kib_per_call": 260.1 + 675.8 + 1195.7 + 128.0,
+        "source_sha256_16": "9a7b80bd3eb358f0",
+        "fetch_kib_per_call": 12028.7 + 184115.6 + 90280.8 + 905.6,
+        "write_kib_per_call": 260.2 + 675.8 + 1195.7 + 128.0,
         "fetch_factor": 2.0,
         "write_factor": 1.0,
         "profile": "profiles/layer_dsv2_decode_kernel_trace_counters.md",
@@ -70,12 +71,13 @@ TRAFFIC_RECORDS = {
                            "paper_2608_21240_amd/csrc/route_device.h",
                            "paper_2608_21240_amd/csrc/expert_ffn_tiles.h",
                            "paper_2608_21240_amd/csrc/expert_ffn_mx_tiles.h",
+                           "paper_2608_21240_amd/csrc/mx_decode.h",
                            "paper_2608_21240_amd/csrc/tile_index.h",
                            "paper_2608_21240_amd/csrc/combine.hip",
                            "paper_2608_21240_amd/csrc/spice_internal.h"),
-        "source_sha256_16": "85a4b3319e438b10",
-        "fetch_kib_per_call": 12026.7 + 55328.1 + 26318.2 + 903.1,
-        "write_kib_per_call": 260.0 + 675.9 + 1195.9 + 128.0,
+        "source_sha256_16": "9a7b80bd3eb358f0",
+        "fetch_kib_per_call": 12031.6 + 55308.9 + 26267.6 + 903.1,
+        "write_kib_per_call": 260.1 + 675.9 + 1195.9 + 128.0,
         "fetch_factor": 2.0,
         "write_factor": 1.0,
         "profile": "profiles/ffn_dsv2_decode_T32_mxfp4.md",
@@ -86,8 +88,8 @@ TRAFFIC_RECORDS = {
                            "paper_2608_21240_amd/csrc/expert_ffn_tiles.h",
                            "paper_2608_21240_amd/csrc/tile_index.h",
                            "paper_2608_21240_amd/csrc/spice_internal.h"),
-        "source_sha256_16": "8ebc4e31dbfbbff5",
-        "fetch_kib_per_call": 189111.0 + 96795.7,
+        "source_sha256_16": "c8d0184604122224",
+        "fetch_kib_per_call": 189111.8 + 96776.7,
         "write_kib_per_call": 462.4 + 1452.0,
         "fetch_factor": 2.0,
         "write_factor": 1.0,
@@ -96,11 +98,12 @@ TRAFFIC_RECORDS = {
     "mxfp4": {
         "kernel_sources": ("paper_2608_21240_amd/csrc/expert_ffn_mx.hip",
                            "paper_2608_21240_amd/csrc/expert_ffn_mx_tiles.h",
+                           "paper_2608_21240_amd/csrc/mx_decode.h",
                            "paper_2608_21240_amd/csrc/expert_ffn_tiles.h",
                            "paper_2608_21240_amd/csrc/tile_index.h",
                            "paper_2608_21240_amd/csrc/spice_internal.h"),
-        "source_sha256_16": "562f86020ed6b351",
-        "fetch_kib_per_call": 60286.4 + 32786.7,
+        "source_sha256_16": "9f92c88ba9b965c5",
+        "fetch_kib_per_call": 60284.4 + 32795.2,
         "write_kib_per_call": 462.6 + 1452.0,
         "fetch_factor": 2.0,
         "write_factor": 1.0,
