@@ -790,7 +790,7 @@ def prefill_main(args):
                    "experts": s.n_experts, "top_k": s.top_k, "inter": s.inter, "shared_inter": s.shared_inter,
                    "lore_rank": s.lore_rank, "resident": args.resident, "tokens": T},
         "roofline": {"bound": "mfma", "kernel": "grouped expert FFN call: expert_gemm_kernel up + down "
-                                                "(moe_expert_ffn_grouped, T >= 256)",
+                                                "(moe_expert_ffn_grouped)",
                      "achieved": round(achieved, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                      "flop_per_launch": flops, "avg_launch_us": round(float(ffn_ms.mean() * 1e3), 1)},
